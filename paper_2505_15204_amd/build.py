@@ -17,7 +17,8 @@ LIB = os.path.join(PKG, "libblink.so")
 UNITS = [("kernels.hip", []), ("persistent.hip", []), ("api.hip", []), ("correlate.hip", []),
          ("split.hip", ["-DBLINK_SPLIT_PREC=1"]), ("split.hip", ["-DBLINK_SPLIT_PREC=2"]),
          ("staged.hip", ["-DBLINK_STAGED_PREC=0"]), ("staged.hip", ["-DBLINK_STAGED_PREC=1"]),
-         ("staged.hip", ["-DBLINK_STAGED_PREC=2"])]
+         ("staged.hip", ["-DBLINK_STAGED_PREC=2"]), ("fold_bin.hip", []), ("fold.hip", ["-DBLINK_FOLD_PREC=0"]),
+         ("fold.hip", ["-DBLINK_FOLD_PREC=1"]), ("fold.hip", ["-DBLINK_FOLD_PREC=2"])]
 SOURCES = sorted({os.path.join(CSRC, f) for f, _ in UNITS})
 
 HIPCC_FLAGS = [

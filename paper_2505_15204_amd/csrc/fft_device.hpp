@@ -125,6 +125,8 @@ __device__ __forceinline__ void dft(float2* v) {
 // LDS banks, and one cache line per 16 values when the table is read from global memory.
 constexpr int kTwA = 16 * 16 + 16;
 __host__ __device__ constexpr int tw_size(int logn) { return kTwA + (logn >= 9 ? (1 << logn) : 0); }
+// Behind it, at tw + tw_size: the linear table exp(+2 pi i t / N), t < N (the folded path).
+__host__ __device__ constexpr int tw_total(int logn) { return tw_size(logn) + (1 << logn); }
 
 template <int NS>
 __device__ __forceinline__ float2 stage_twiddle(const float2* __restrict__ tw, int k, int m) {

@@ -28,7 +28,7 @@ namespace blink {
 // argument, rounded to FP32. Unused rows of A (m >= R1) hold zero.
 __global__ void k_twiddles(float2* tw, int logn) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= tw_size(logn)) return;
+  if (j >= tw_total(logn)) return;
   const int n = 1 << logn;
   const int r1 = logn <= 4 ? 1 : (logn >= 8 ? 16 : n / 16);
   long num = 0, den = 1;
@@ -41,6 +41,9 @@ __global__ void k_twiddles(float2* tw, int logn) {
   } else if (j < kTwA) {              // D: 16-point DFT entries
     num = j - 256;
     den = 16;
+  } else if (j >= tw_size(logn)) {    // linear table
+    num = j - tw_size(logn);
+    den = n;
   } else {                            // B: row m, column k
     const int m = (j - kTwA) / 256, k = (j - kTwA) % 256;
     num = (long)k * m;
@@ -51,7 +54,7 @@ __global__ void k_twiddles(float2* tw, int logn) {
   tw[j] = used ? make_float2((float)c, (float)s) : make_float2(0.f, 0.f);
 }
 
-int twiddle_table_size(int logn) { return tw_size(logn); }
+int twiddle_table_size(int logn) { return tw_total(logn); }
 
 // ---------------------------------------------------------------- split-form DFT operands
 __global__ void k_dft_operands(const float2* __restrict__ tw, uint4* ops) {
@@ -66,7 +69,7 @@ hipError_t launch_dft_operands(const float2* tw, uint4* ops, hipStream_t s) {
 }
 
 hipError_t launch_twiddles(float2* tw, int logn, hipStream_t s) {
-  const int n = tw_size(logn);
+  const int n = tw_total(logn);
   k_twiddles<<<(n + 255) / 256, 256, 0, s>>>(tw, logn);
   return hipGetLastError();
 }

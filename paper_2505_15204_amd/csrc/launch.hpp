@@ -96,6 +96,74 @@ struct RowArgs {
 };
 hipError_t launch_row_c2r(const RowArgs& a, int n_img, int tpb, int prec, const float2* tw, hipStream_t s);
 
+// ---------------------------------------------------------------- folded imaging path (fold_device.hpp)
+constexpr int kFoldDiag = 16;              // placements of a segment stored in the jagged diagonals
+constexpr int kFoldCells = 8192;           // most folded cells (M N / 2) of a class
+constexpr int kFoldMinLogn = 6, kFoldMaxLogn = 12;
+constexpr int kFoldMaxB = 16 * 1024;       // baselines a binning workgroup keeps in registers
+// Rows of a residue class: M N = 16384 (two classes fill the LDS of one compute unit), at most the
+// whole grid.
+constexpr int fold_rows(int logn) { return logn <= 7 ? 1 << logn : kFoldCells * 2 >> logn; }
+
+// Row table of a pair: for each of up to 8 waves of the imaging workgroup, its rows (64 segments of
+// one diagonal) as first placement | flags, padded with empty rows to whole batches, at least two.
+constexpr int kFoldRowBatch = 8;           // rows of a wave whose loads are issued together
+constexpr int kFoldRowsPerWave = 256, kFoldRows = 8 * kFoldRowsPerWave;
+constexpr uint32_t kFoldRowFirst = 1u << 24, kFoldRowLast = 1u << 25;
+// Placements of a pair, with the diagonals padded to whole rows.
+constexpr int fold_entries(int B) { return 2 * B + 64 * kFoldDiag; }
+
+struct FoldHeader {                        // one (time, channel) pair
+  int rows[8];                             // rows of each wave
+  int first_over, n_over;                  // placements beyond the diagonals
+  int ext, kept, occ;                      // columns [0, ext) hold every placement; kept; occupied cells
+  int pad[3];
+};
+
+struct FoldBinArgs {
+  const double* uvw;        // [T][B][3]
+  const double* freq;       // [C]
+  const uint8_t* flags;     // [T][C][B] or null
+  const float2* vis;        // chunk base [Q][P][B]
+  int tc0, Q, C, B, P, logn, logm, uniform, shift;
+  double pixel_scale;
+  int ent_stride;
+  FoldHeader* hdr;          // [Q]
+  uint32_t* rows;           // [Q][kFoldRows]
+  uint32_t* rec;            // [Q][ent_stride]: placement records {8 (kv / M), LDS index << 17}
+  float2* val;              // [Q][P][ent_stride]: the placements' values over the image's weight
+  int32_t* n_out;           // [T][C] or null (global)
+};
+hipError_t launch_fold_bin(const FoldBinArgs& a, hipStream_t s);
+
+struct FoldImage {
+  const FoldHeader* hdr;
+  const uint32_t* rows;
+  const uint32_t* rec;
+  const float2* val;
+  float* out;
+};
+
+struct FoldArgs {
+  const FoldHeader* hdr;
+  const uint32_t* rows;
+  const uint32_t* rec;
+  const float2* val;
+  int logn, n_img, P, uniform, ent_stride;
+  float* images;            // [n_img][N][N]
+  double* weight_sum;       // [n_img] or null
+  const uint4* dft_ops;
+};
+hipError_t launch_fold_image(const FoldArgs& a, int prec, const float2* tw, hipStream_t s);
+
+template <int PREC>
+struct FoldLaunch {
+  static hipError_t image(const FoldArgs& a, const float2* tw, hipStream_t s);
+};
+extern template struct FoldLaunch<BLINK_PREC_FP32>;
+extern template struct FoldLaunch<BLINK_PREC_SPLIT_F16>;
+extern template struct FoldLaunch<BLINK_PREC_SPLIT_BF16>;
+
 // ---------------------------------------------------------------- convolutional gridding
 // Separable exponential-of-semicircle kernel of `width` cells (conv_device.hpp).
 struct ConvParams {

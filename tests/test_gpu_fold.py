@@ -1,0 +1,124 @@
+"""GPU parity of the folded path of blink_image_batch (64 <= N <= 4096, up to 16384 baselines) at the
+edges of its layout: every grid size, one baseline, 64-segment rows and their remainders, image
+counts around the groups of eight, placements that pile up on one cell beyond the diagonals, the
+u = 0 column with its mirrored placements, and the baseline counts on both sides of the path's
+limits (8192 baselines per thread group, 16384 in all). The workspace is filled with 0xFF bytes
+(NaN). Bars as for the other parity tests: weight sums and out-of-grid counts bit-exact, images
+within a relative L2 of 1e-5 (FP32) or 1e-3 (split forms) of the FP64 oracle.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+from image_checks import rel_l2
+
+pytestmark = pytest.mark.gpu
+
+IMAGE_TOL = {0: 1e-5, 1: 1e-3, 2: 1e-3}
+FREQ = 150.0e6
+C_LIGHT = 299792458.0
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as _t
+    if not _t.cuda.is_available():
+        pytest.skip("no GPU")
+    return _t
+
+
+@pytest.fixture(scope="module")
+def ctx(torch):
+    import paper_2505_15204_amd as blink
+    c = blink.Context(0)
+    yield c
+    c.close()
+
+
+def coverage(kind, B, N, g):
+    """Baseline coordinates in cells, [B][2]."""
+    r = N // 2 - 1
+    if kind == "uniform":          # all over the grid, some outside it
+        return g.uniform(-1.1 * r, 1.1 * r, (B, 2))
+    if kind == "pile":             # most baselines in a few cells: runs far beyond the diagonals
+        x = g.integers(-1, 2, (B, 2)).astype(float)
+        x[: B // 4] = g.uniform(-r, r, (B // 4, 2))
+        return x
+    if kind == "column0":          # every placement on the u = 0 column, mirrored there
+        x = g.uniform(-r, r, (B, 2))
+        x[:, 0] = 0.0
+        return x
+    if kind == "row0":             # one folded row
+        x = g.uniform(-r, r, (B, 2))
+        x[:, 1] = 0.0
+        return x
+    raise ValueError(kind)
+
+
+def check(torch, ctx, kind, B, N, weighting, prec, C=1, P=1, shift=True, flag_frac=0.1):
+    import paper_2505_15204_amd as blink
+
+    g = np.random.default_rng(1000 + B + N)
+    dl = 1.0e-3
+    k = FREQ / C_LIGHT * (N * dl)
+    uvw = np.zeros((1, B, 3))
+    uvw[0, :, :2] = coverage(kind, B, N, g) / k
+    freq = np.full(C, FREQ)
+    vis = (g.normal(size=(1, C, P, B)) + 1j * g.normal(size=(1, C, P, B))).astype(np.complex64)
+    flags = (g.random((1, C, B)) < flag_frac).astype(np.uint8)
+    print(f"[gpu-case] fold {kind} B={B} N={N} w={weighting} prec={prec} C={C} P={P} shift={shift}", flush=True)
+    sys.stdout.flush()
+    d = "cuda:0"
+    ws = torch.full((blink.image_batch_workspace_size(1, C, P, B, N, weighting, prec),), 255, dtype=torch.uint8, device=d)
+    res = ctx.blink_image_batch(torch.from_numpy(vis).to(d), torch.from_numpy(flags).to(d), torch.from_numpy(uvw).to(d),
+                                torch.from_numpy(freq).to(d), N, dl, weighting, precision=prec, shift=shift, workspace=ws)
+    torch.cuda.synchronize()
+    ref = oracle.image_batch(vis, flags, uvw, freq, N, dl, weighting, shift=shift)
+    assert np.array_equal(res["weight_sum"].cpu().numpy(), ref["weight_sum"])
+    assert np.array_equal(res["n_out"].cpu().numpy(), ref["n_out"])
+    got = res["images"].cpu().numpy()
+    for c in range(C):
+        for p in range(P):
+            want = ref["images"][0, c, p]
+            if not want.any():
+                assert not got[0, c, p].any()
+            else:
+                assert rel_l2(got[0, c, p], want) <= IMAGE_TOL[prec], (c, p)
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+@pytest.mark.parametrize("weighting", [0, 1])
+@pytest.mark.parametrize("N", [64, 128, 256, 512, 1024, 2048, 4096])
+def test_every_size(torch, ctx, N, weighting, prec):
+    check(torch, ctx, "uniform", 333, N, weighting, prec)
+
+
+@pytest.mark.parametrize("B", [1, 2, 63, 64, 65, 1023, 1025])
+def test_row_remainders(torch, ctx, B):
+    check(torch, ctx, "uniform", B, 256, 0, 0, shift=B % 2 == 0)
+
+
+@pytest.mark.parametrize("weighting", [0, 1])
+@pytest.mark.parametrize("kind,B,N", [("pile", 3000, 128), ("pile", 3000, 1024), ("column0", 2000, 256),
+                                      ("column0", 2000, 4096), ("row0", 2000, 512), ("row0", 700, 64)])
+def test_crowded_cells(torch, ctx, kind, B, N, weighting):
+    check(torch, ctx, kind, B, N, weighting, 0, P=2)
+
+
+@pytest.mark.parametrize("weighting", [0, 1])
+@pytest.mark.parametrize("B", [8191, 8192, 8193, 16384, 16385])
+def test_baseline_limits(torch, ctx, B, weighting):
+    check(torch, ctx, "uniform", B, 128, weighting, 0)
+    check(torch, ctx, "column0", B, 128, weighting, 0)
+
+
+@pytest.mark.parametrize("C", [7, 8, 9, 17])
+def test_image_counts(torch, ctx, C):
+    check(torch, ctx, "uniform", 100, 128, 0, 0, C=C, P=1)
+
+
+def test_everything_flagged(torch, ctx):
+    check(torch, ctx, "uniform", 500, 256, 0, 0, P=2, flag_frac=1.1)
+    check(torch, ctx, "uniform", 500, 256, 1, 0, P=2, flag_frac=1.1)
