@@ -986,7 +986,7 @@ blink_status blink_dedisperse(blink_ctx ctx, const float* images, int T, int C, 
   if (e != hipSuccess) return hip_fail(ctx, e, "delay table copy");
   {
     KernelTimer kt(ctx, BLINK_KERNEL_DEDISPERSE, s);
-    e = blink::launch_dedisperse(images, C, logn, (const int*)workspace, n_dm, t_out, out, s);
+    e = blink::launch_dedisperse(images, C, logn, (const int*)workspace, delays, n_dm, t_out, out, s);
   }
   if (e != hipSuccess) return hip_fail(ctx, e, "de-dispersion kernel");
   return BLINK_OK;
