@@ -23,6 +23,8 @@
 
 namespace blink {
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 // ---------------------------------------------------------------- twiddles
 // The stage-ordered table of one size N (fft_device.hpp): FP64 sincospi of an exact dyadic
 // argument, rounded to FP32. Unused rows of A (m >= R1) hold zero.
@@ -165,10 +167,6 @@ hipError_t launch_grid_colfft_conv(const ColArgs& a, int n_img, ConvParams cp, i
   }
 }
 
-// ---------------------------------------------------------------- image averages
-// Averages of images [T][C][P][N][N] over the axes in `axes` (1 time, 2 channel, 4 polarisation;
-// Sections 7.2 and 7.3 average over time and over the band, the polarisation average of XX and YY
-// is Stokes I). One thread per 4 consecutive pixels of one output image, FP64 sums.
 // ---------------------------------------------------------------- visibility corrections
 // Antenna pair (i, j), i > j, of baseline b = i (i - 1) / 2 + j: the lower-triangular order in
 // which the correlation step stores visibilities (Section 6.2.2).
@@ -220,36 +218,99 @@ hipError_t launch_correct_vis(const CorrArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void k_image_average(const float4* __restrict__ in, int T, int C, int P, long nn4,
-                                                       int axes, float4* __restrict__ out) {
-  const int To = (axes & 1) ? 1 : T, Co = (axes & 2) ? 1 : C, Po = (axes & 4) ? 1 : P;
-  const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (long)To * Co * Po * nn4) return;
-  const long img = gid / nn4, px = gid - img * nn4;
+// ---------------------------------------------------------------- image averages
+// Averages of images [T][C][P][N][N] over the axes in `axes` (1 time, 2 channel, 4 polarisation;
+// Sections 7.2 and 7.3 average over time and over the band, the polarisation average of XX and YY
+// is Stokes I). Four consecutive pixels of one output per lane, FP64 sums. The inputs of an output
+// are runs of n1 images at a stride of s1, n2 runs at a stride of s2; groups of WIDTH waves take equal
+// parts of the inputs of the same 256 WIDTH pixels and their sums meet in LDS, which keeps enough
+// loads in flight for small images too (8 per lane). Bound by reading the inputs: 6.1 TB/s of the
+// 6.2 that a copy reaches.
+struct AvgRuns {
+  int n1, n2;
+  long s1, s2;                                  // in images
+};
+
+template <int SLICES, int WIDTH>
+__global__ __launch_bounds__(64 * SLICES * WIDTH) void k_image_average(const f32x4* __restrict__ in, int C, int P, long nn4,
+                                                                int axes, int Co, int Po, AvgRuns r,
+                                                                f32x4* __restrict__ out) {
+  __shared__ double part[SLICES > 1 ? SLICES - 1 : 1][4][64 * WIDTH];
+  const int lane = threadIdx.x % (64 * WIDTH), slice = __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * WIDTH));
+  const long blocks = (nn4 + 64 * WIDTH - 1) / (64 * WIDTH), img = blockIdx.x / blocks;
+  const long px = (blockIdx.x - img * blocks) * (64 * WIDTH) + lane;
   const int po = (int)(img % Po), co = (int)((img / Po) % Co), to = (int)(img / ((long)Po * Co));
-  const int t0 = (axes & 1) ? 0 : to, t1 = (axes & 1) ? T : to + 1;
-  const int c0 = (axes & 2) ? 0 : co, c1 = (axes & 2) ? C : co + 1;
-  const int p0 = (axes & 4) ? 0 : po, p1 = (axes & 4) ? P : po + 1;
-  double ax = 0.0, ay = 0.0, az = 0.0, aw = 0.0;
-  for (int t = t0; t < t1; ++t)
-    for (int c = c0; c < c1; ++c)
-      for (int p = p0; p < p1; ++p) {
-        const float4 v = in[(((long)t * C + c) * P + p) * nn4 + px];
-        ax += v.x;
-        ay += v.y;
-        az += v.z;
-        aw += v.w;
-      }
-  const double inv = 1.0 / ((double)(t1 - t0) * (c1 - c0) * (p1 - p0));
-  out[gid] = make_float4((float)(ax * inv), (float)(ay * inv), (float)(az * inv), (float)(aw * inv));
+  const long first = ((long)((axes & 1) ? 0 : to) * C + ((axes & 2) ? 0 : co)) * P + ((axes & 4) ? 0 : po);
+  const long n = (long)r.n1 * r.n2;
+  const f32x4* src = in + first * nn4 + (px < nn4 ? px : 0);
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  long k = n * slice / SLICES;
+  const long k1 = n * (slice + 1) / SLICES;
+  while (k < k1) {                              // uniform over the wave
+    const long run = k / r.n1, at = k - run * r.n1;
+    const int m = (int)(r.n1 - at < k1 - k ? r.n1 - at : k1 - k);
+    const f32x4* p = src + (run * r.s2 + at * r.s1) * nn4;
+    const long step = r.s1 * nn4;
+    int i = 0;
+    for (; i + 8 <= m; i += 8, p += 8 * step) {
+      f32x4 v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = __builtin_nontemporal_load(p + j * step);
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a[q] += (double)v[j][q];
+    }
+    for (; i < m; ++i, p += step) {
+      const f32x4 v = __builtin_nontemporal_load(p);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a[q] += (double)v[q];
+    }
+    k += m;
+  }
+  if constexpr (SLICES > 1) {
+    if (slice > 0)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) part[slice - 1][q][lane] = a[q];
+    __syncthreads();
+    if (slice > 0) return;
+    for (int s = 0; s < SLICES - 1; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a[q] += part[s][q][lane];
+  }
+  const double inv = 1.0 / (double)n;
+  if (px < nn4) out[img * nn4 + px] = f32x4{(float)(a[0] * inv), (float)(a[1] * inv), (float)(a[2] * inv), (float)(a[3] * inv)};
 }
 
 hipError_t launch_image_average(const float* in, int T, int C, int P, int logn, int axes, float* out, hipStream_t s) {
   const long nn4 = (1L << (2 * logn)) / 4;
-  const long n_out = (long)((axes & 1) ? 1 : T) * ((axes & 2) ? 1 : C) * ((axes & 4) ? 1 : P) * nn4;
-  if (n_out <= 0) return hipSuccess;
-  k_image_average<<<(unsigned)((n_out + 255) / 256), 256, 0, s>>>((const float4*)in, T, C, P, nn4, axes,
-                                                                    (float4*)out);
+  const int To = (axes & 1) ? 1 : T, Co = (axes & 2) ? 1 : C, Po = (axes & 4) ? 1 : P;
+  const long n_img = (long)To * Co * Po;
+  if (n_img * nn4 <= 0) return hipSuccess;
+  // the averaged axes as runs: polarisation and channel merge into one when both are averaged (or
+  // there is one polarisation), channel and time likewise
+  struct { long n, s; } d[3] = {{(axes & 4) ? P : 1, 1}, {(axes & 2) ? C : 1, P}, {(axes & 1) ? T : 1, (long)C * P}}, m[3];
+  int nd = 0;
+  for (auto& x : d) {
+    if (x.n == 1) continue;
+    if (nd > 0 && m[nd - 1].n * m[nd - 1].s == x.s) m[nd - 1].n *= x.n;
+    else m[nd++] = {x.n, x.s};
+  }
+  AvgRuns r{1, 1, 1, 1};
+  if (nd > 0) r.n1 = (int)m[0].n, r.s1 = m[0].s;
+  if (nd > 1) r.n2 = (int)m[1].n, r.s2 = m[1].s;   // (three separate axes always merge)
+  const long n = (long)r.n1 * r.n2;
+  const f32x4* src = (const f32x4*)in;
+  f32x4* dst = (f32x4*)out;
+  auto blocks = [&](int width) { return (unsigned)((nn4 + 64 * width - 1) / (64 * width) * n_img); };
+  if ((nn4 + 63) / 64 * n_img > 0x7fffffffL) return hipErrorInvalidValue;
+  // Below 16 inputs the sum is short; below 2048 blocks of 256 pixels (256^2 and smaller, one output)
+  // more waves per output are needed than the 8 slices of the wider form give: 8400 images of
+  // 256^2 take 337 us with 16 slices, 3886 us with one; 1536 of 1024^2 1055 us with 8 slices of 512
+  // pixels, 1078 with 4 of 256, 1228 with 4 of 1024, 1211 with one (one thread per pixel quad).
+  if (n < 16) k_image_average<1, 1><<<blocks(1), 64, 0, s>>>(src, C, P, nn4, axes, Co, Po, r, dst);
+  else if (blocks(1) >= 2048) k_image_average<8, 2><<<blocks(2), 1024, 0, s>>>(src, C, P, nn4, axes, Co, Po, r, dst);
+  else k_image_average<16, 1><<<blocks(1), 1024, 0, s>>>(src, C, P, nn4, axes, Co, Po, r, dst);
   return hipGetLastError();
 }
 
