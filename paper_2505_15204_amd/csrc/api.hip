@@ -1289,10 +1289,85 @@ blink::DescArgs desc_args(blink_ctx ctx, const DescCall& c, int max_logn, int bl
   return a;
 }
 
+// Staged form, folded (fold_device.hpp): the descriptor pass, then for as many positions of the order
+// as the workspace holds at a time one binning launch and one launch that images them.
+struct FoldDescLayout {
+  size_t valid, order, counter, status, sizes, hdr, rows, rec, val, total;
+  int ent_stride;
+  bool ok;
+};
+
+FoldDescLayout fold_desc_layout(size_t n_img, size_t n_pos, size_t max_b) {
+  Carve c;
+  FoldDescLayout L;
+  L.ent_stride = blink::fold_entries((int)max_b);
+  L.valid = c.take(n_img, sizeof(int));
+  L.order = c.take(n_img, sizeof(int));
+  L.counter = c.take(1, sizeof(int));
+  L.status = c.take(1, sizeof(int));
+  L.sizes = c.take(13, sizeof(int4));
+  L.hdr = c.take(n_pos, sizeof(blink::FoldHeader));
+  L.rows = c.take(n_pos, blink::kFoldRows * sizeof(uint32_t));
+  L.rec = c.take(n_pos, (size_t)L.ent_stride * sizeof(uint32_t));
+  L.val = c.take(n_pos, (size_t)L.ent_stride * sizeof(float2));
+  L.total = c.off;
+  L.ok = c.ok;
+  return L;
+}
+
+blink_status run_desc_folded(blink_ctx ctx, const DescCall& c, int max_logn, size_t n_pos, hipStream_t s) {
+  DeviceGuard g(ctx->device);
+  if (g.err != hipSuccess) return hip_fail(ctx, g.err, "hipSetDevice");
+  const FoldDescLayout L = fold_desc_layout(c.n_img, n_pos, c.max_b);
+  char* ws = (char*)c.ws;
+  blink::DescArgs a = desc_args(ctx, c, max_logn, desc_block_for(ctx, c.weighting));
+  a.status = c.status ? c.status : (int32_t*)(ws + L.status);
+  a.valid = (int*)(ws + L.valid);
+  a.order = (int*)(ws + L.order);
+  a.counter = (int*)(ws + L.counter);
+  a.sizes = (int4*)(ws + L.sizes);
+  a.hdr = (blink::FoldHeader*)(ws + L.hdr);
+  a.rows = (uint32_t*)(ws + L.rows);
+  a.rec = (uint32_t*)(ws + L.rec);
+  a.val = (float2*)(ws + L.val);
+  a.ent_stride = L.ent_stride;
+  hipError_t e;
+  {
+    KernelTimer kt(ctx, BLINK_KERNEL_DESC_PREP, s);
+    e = blink::launch_desc_prep(a, s);
+  }
+  for (size_t p0 = 0; p0 < (size_t)c.n_img && e == hipSuccess; p0 += n_pos) {
+    a.pos0 = (int)p0;
+    a.n_pos = (int)((size_t)c.n_img - p0 < n_pos ? (size_t)c.n_img - p0 : n_pos);
+    {
+      KernelTimer kt(ctx, BLINK_KERNEL_BIN, s);
+      e = blink::launch_fold_bin_desc(a, s);
+    }
+    if (e != hipSuccess) break;
+    // items of images that do not share pixels: one per 16384 pixels and one per smaller image, with
+    // every size's count rounded up to 8; at most n_pos images of the largest size
+    const int64_t most = (int64_t)a.n_pos * ((1 << max_logn) / blink::fold_rows(max_logn)) + 80;
+    int64_t items = c.images_len / (2 * blink::kFoldCells) + a.n_pos + 80;
+    if (items > most) items = most;
+    KernelTimer kt(ctx, BLINK_KERNEL_GRID_COLFFT, s);
+    e = blink::launch_fold_desc(a, c.precision, (unsigned)(items < 0x7fffffff ? items : 0x7fffffff), s);
+  }
+  if (e != hipSuccess) return hip_fail(ctx, e, "uneven-batch folded kernels");
+  return BLINK_OK;
+}
+
 // Staged form: the descriptor pass, one binning launch, then for every grid size from the largest
 // down and every chunk slot reserved for it, the chunk's column launch and row launch with the
 // batched path's plan for that size (strip width, strips per workgroup, row block).
 blink_status run_desc_staged(blink_ctx ctx, const DescCall& c, int max_logn, hipStream_t s) {
+  if (c.max_b <= blink::kFoldMaxB && staged_layout(c.n_img, c.max_b, c.max_n).total <= c.ws_bytes) {
+    // Folded wherever the binning keeps an image's baselines in registers (400 images, 2721 -> 1500 us),
+    // at least 64 images at a time (or the batch): fewer would leave the binning launches idle.
+    const size_t n_pos = largest_fitting_chunk((size_t)c.n_img, c.ws_bytes, [&](size_t n) {
+      return fold_desc_layout(c.n_img, n, c.max_b).total;
+    });
+    if (n_pos >= (size_t)(c.n_img < 64 ? c.n_img : 64)) return run_desc_folded(ctx, c, max_logn, n_pos, s);
+  }
   StagedLayout L = staged_layout(c.n_img, c.max_b, c.max_n);
   if (!L.ok || L.total > c.ws_bytes)
     return fail(ctx, BLINK_ERR_SIZE, "workspace of %zu bytes is smaller than the %zu bytes the staged form needs",

@@ -185,7 +185,7 @@ __device__ __forceinline__ void fold_bin(const double* __restrict__ uvw, const u
   // Row table: the rows (diagonal j of 64 segments) of each wave of the imaging workgroup. Chunk
   // c of 64 segments goes to the waves in turn, forth and back, so that the long ones spread.
   {
-    const int nw = (M << logn) / 2048, chunks = (sh.cum[0] + 63) / 64;
+    const int nw = (M << logn) >= 4096 ? (M << logn) / 2048 : 1, chunks = (sh.cum[0] + 63) / 64;
     auto depth = [&](int c) {                    // diagonals of chunk c
       int d = 0;
       for (int j = 0; j < kFoldDiag; ++j) d += sh.cum[j] > 64 * c;
@@ -343,7 +343,48 @@ __global__ __launch_bounds__(kFoldThreads, NB > 8 ? 4 : 8) void k_fold_bin(FoldB
                                a.n_out ? a.n_out + tc : nullptr, sh);
 }
 
+// Uneven batches: workgroup w bins the image at position pos0 + w of the descriptor pass's order.
+template <int NB, bool UNIFORM, int STAGE>
+__global__ __launch_bounds__(kFoldThreads, NB > 8 ? 4 : 8) void k_fold_bin_desc(DescArgs a) {
+  __shared__ FoldShared<STAGE> sh;
+  const int at = blockIdx.x, img = a.order[a.pos0 + at];
+  if (!a.valid[img]) return;                       // uniform over the workgroup
+  const blink_image_desc d = a.desc[img];
+  const int logn = 31 - __clz(d.grid_n), logm = 31 - __clz(fold_rows(logn));
+  const double k = (d.freq_hz / kSpeedOfLight) * ((double)d.grid_n * d.pixel_scale);
+  // The loads of an image without baselines, whose values are not used, go to its own header.
+  const bool some = d.n_baselines > 0;
+  const double* uvw = some ? a.uvw + 3 * d.uvw_offset : reinterpret_cast<const double*>(a.hdr + at);
+  const float2* vis = some ? a.vis + d.vis_offset : reinterpret_cast<const float2*>(a.hdr + at);
+  fold_bin<NB, UNIFORM, STAGE>(uvw, some && a.flags ? a.flags + d.flag_offset : nullptr, d.n_baselines, k, logn, logm,
+                               a.shift, vis, 1, 0, a.hdr + at,
+                               a.rows + (size_t)at * kFoldRows, a.rec + (size_t)at * a.ent_stride,
+                               a.val + (size_t)at * a.ent_stride, 0, a.n_out ? a.n_out + img : nullptr, sh);
+}
+
 }  // namespace
+
+hipError_t launch_fold_bin_desc(const DescArgs& a, hipStream_t s) {
+  if (a.n_pos <= 0) return hipSuccess;
+  if (a.max_b > kFoldMaxB) return hipErrorInvalidValue;
+  if (a.max_b <= 8 * kFoldThreads) {
+    if (a.weighting) k_fold_bin_desc<8, true, 68 * 1024><<<a.n_pos, kFoldThreads, 0, s>>>(a);
+    else k_fold_bin_desc<8, false, 68 * 1024><<<a.n_pos, kFoldThreads, 0, s>>>(a);
+  } else {
+    if (a.weighting) k_fold_bin_desc<16, true, 132 * 1024><<<a.n_pos, kFoldThreads, 0, s>>>(a);
+    else k_fold_bin_desc<16, false, 132 * 1024><<<a.n_pos, kFoldThreads, 0, s>>>(a);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_fold_desc(const DescArgs& a, int prec, unsigned items, hipStream_t s) {
+  switch (prec) {
+    case BLINK_PREC_FP32: return FoldLaunch<BLINK_PREC_FP32>::desc(a, items, s);
+    case BLINK_PREC_SPLIT_F16: return FoldLaunch<BLINK_PREC_SPLIT_F16>::desc(a, items, s);
+    case BLINK_PREC_SPLIT_BF16: return FoldLaunch<BLINK_PREC_SPLIT_BF16>::desc(a, items, s);
+    default: return hipErrorInvalidValue;
+  }
+}
 
 hipError_t launch_fold_bin(const FoldBinArgs& a, hipStream_t s) {
   if (a.Q <= 0) return hipSuccess;

@@ -96,18 +96,22 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t fold_rsrc(const void* p, int b
 
 // Residue class r of one image: see the head of this file. sbuf holds
 // M / 2 row pairs (slot p of the class at (p / 2) NP + pad((p % 2) N/2 + column)), later each pair's
-// transform buffer, and one word behind them for the padding placements.
-template <int LOGN, int M, int PREC>
+// transform buffer, and one word behind them for the padding placements. The workgroup has BLOCK >=
+// M N / 32 threads; the others only join the barriers and the loops over columns.
+template <int LOGN, int M, int PREC, int BLOCK>
 __device__ __forceinline__ void fold_class(const FoldImage& im, int r, float2* sbuf, float2* s_w,
                                            const float2* __restrict__ tw, const float2* __restrict__ lin, SplitCtx sp) {
   using P = FftPlan<LOGN>;
   using FR = FoldRadix<M>;
-  constexpr int N = P::N, T = P::T, NP = P::NP, HALF = N / 2, R = N / M, NT = M * N / 32, A = FR::A, B = FR::B;
-  constexpr bool SPLIT = PREC != kPrecFp32;
+  constexpr int N = P::N, T = P::T, NP = P::NP, HALF = N / 2, R = N / M, NT = (M / 2) * T, NW = NT >= 64 ? NT / 64 : 1;
+  constexpr int A = FR::A, B = FR::B;
+  constexpr bool SPLIT = PREC != kPrecFp32 && LOGN >= 4;
+  static_assert(BLOCK % 64 == 0 && BLOCK >= NT, "whole waves");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int ext = im.hdr->ext, first_over = im.hdr->first_over, n_over = im.hdr->n_over, n_ent = first_over + n_over;
-  const int nrows = im.hdr->rows[wave];
+  const bool folds = BLOCK / 64 == NW || wave < NW;   // uniform over the wave
+  const int nrows = folds ? im.hdr->rows[wave] : 0;
   const uint32_t* rows = im.rows + wave * kFoldRowsPerWave;
   const __amdgpu_buffer_rsrc_t rv = fold_rsrc(im.val, n_ent * 8), rr = fold_rsrc(im.rec, n_ent * 4);
   auto load_val = [&](int at, int base) {
@@ -159,17 +163,22 @@ __device__ __forceinline__ void fold_class(const FoldImage& im, int r, float2* s
   // padded LDS index of a + b T (a <= T): one base plus compile-time steps when T is a multiple of 16
   auto pad_at = [](int a, int b) { return T % 16 == 0 ? pad_index(a) + pad_offset(b * T) : pad_index(a + b * T); };
   // row pairs: pair j holds the rows of slots 2 j and 2 j + 1
-  const int j = T % 64 == 0 ? __builtin_amdgcn_readfirstlane(tid / T) : tid / T, lt = tid % T;
+  const bool active = BLOCK == NT || tid < NT;
+  const int jt = active ? tid / T : 0, j = T % 64 == 0 ? __builtin_amdgcn_readfirstlane(jt) : jt, lt = tid % T;
   float2* buf = sbuf + j * NP;
   // The first two batches are requested whatever their number (the table holds that many rows for
   // every wave, empty ones reading placement 0), so that the header and the table cost one wait.
   Rows qa, qb;
-  load_rows(qa, 0);
-  load_rows(qb, kFoldRowBatch);
+  if (folds) {
+    load_rows(qa, 0);
+    load_rows(qb, kFoldRowBatch);
+  }
+  if (active) {
 #pragma unroll
-  for (int i = 0; i < P::R; ++i) buf[lt + i * T] = make_float2(0.f, 0.f);
-  for (int i = N + lt; i < NP; i += T) buf[i] = make_float2(0.f, 0.f);
-  for (int i = tid; i < R; i += NT) s_w[i] = lin[(r * i * M) & (N - 1)];   // w_R^(r h)
+    for (int i = 0; i < P::R; ++i) buf[lt + i * T] = make_float2(0.f, 0.f);
+    for (int i = N + lt; i < NP; i += T) buf[i] = make_float2(0.f, 0.f);
+  }
+  for (int i = tid; i < R; i += BLOCK) s_w[i] = lin[(r * i * M) & (N - 1)];   // w_R^(r h)
   if constexpr (SPLIT) {
     if (tid == 0) *sp.s_max = 0u;
   }
@@ -189,11 +198,11 @@ __device__ __forceinline__ void fold_class(const FoldImage& im, int r, float2* s
       atomicAdd(&d->y, v.y);
     };
     if (tid < n_over) add(xv, xr);
-    for (int x = first_over + tid + NT; x < n_ent; x += NT) add(im.val[x], im.rec[x]);
+    for (int x = first_over + tid + BLOCK; x < n_ent; x += BLOCK) add(im.val[x], im.rec[x]);
     __syncthreads();
   }
   // M-point transforms of the columns below the extent, in place, with the factors w_N^(r k)
-  for (int i = tid; i < B * HALF; i += NT) {
+  for (int i = tid; i < B * HALF; i += BLOCK) {
     const int c = i % HALF, n2 = HALF % 64 == 0 ? __builtin_amdgcn_readfirstlane(i / HALF) : i / HALF;
     const int pc = pad_index(c);
     if (c >= ext) continue;
@@ -214,7 +223,7 @@ __device__ __forceinline__ void fold_class(const FoldImage& im, int r, float2* s
   }
   __syncthreads();
   if constexpr (B > 1) {
-    for (int i = tid; i < A * HALF; i += NT) {
+    for (int i = tid; i < A * HALF; i += BLOCK) {
       const int c = i % HALF, k1 = i / HALF, pc = pad_index(c);
       if (c >= ext) continue;
       float2 v[B];
@@ -244,8 +253,10 @@ __device__ __forceinline__ void fold_class(const FoldImage& im, int r, float2* s
   auto row_at = [&](int p) { return o + (size_t)(FR::row_of(p) * R) * N; };
   if constexpr (SPLIT) {
     stage_sync<T>();                           // every load of the row pair is done
+    if (active) {
 #pragma unroll
-    for (int m = 0; m < P::R; ++m) buf[pad_at(lt, m)] = v[m];
+      for (int m = 0; m < P::R; ++m) buf[pad_at(lt, m)] = v[m];
+    }
     __syncthreads();
     fft_inverse_split<LOGN, PREC, false, true>(sbuf, M / 2, tw, [](int, int) { return make_float2(0.f, 0.f); },
                                                [&](int c, int e, float2 z) {
@@ -258,7 +269,7 @@ __device__ __forceinline__ void fold_class(const FoldImage& im, int r, float2* s
     fft_inverse<LOGN, false>(v, buf, tw, lt, [&](int e, float2 z) {
       __builtin_nontemporal_store(z.x, &o1[e]);
       __builtin_nontemporal_store(z.y, &o2[e]);
-    });
+    }, active);
   }
 }
 

@@ -97,9 +97,10 @@ struct RowArgs {
 hipError_t launch_row_c2r(const RowArgs& a, int n_img, int tpb, int prec, const float2* tw, hipStream_t s);
 
 // ---------------------------------------------------------------- folded imaging path (fold_device.hpp)
+struct DescArgs;
 constexpr int kFoldDiag = 16;              // placements of a segment stored in the jagged diagonals
 constexpr int kFoldCells = 8192;           // most folded cells (M N / 2) of a class
-constexpr int kFoldMinLogn = 6, kFoldMaxLogn = 12;
+constexpr int kFoldMinLogn = 6;            // smallest grid that blink_image_batch images this way
 constexpr int kFoldMaxB = 16 * 1024;       // baselines a binning workgroup keeps in registers
 // Rows of a residue class: M N = 16384 (two classes fill the LDS of one compute unit), at most the
 // whole grid.
@@ -159,6 +160,7 @@ hipError_t launch_fold_image(const FoldArgs& a, int prec, const float2* tw, hipS
 template <int PREC>
 struct FoldLaunch {
   static hipError_t image(const FoldArgs& a, const float2* tw, hipStream_t s);
+  static hipError_t desc(const DescArgs& a, unsigned items, hipStream_t s);
 };
 extern template struct FoldLaunch<BLINK_PREC_FP32>;
 extern template struct FoldLaunch<BLINK_PREC_SPLIT_F16>;
@@ -226,6 +228,11 @@ hipError_t launch_image_average(const float* in, int T, int C, int P, int logn, 
 
 struct DescArgs;
 
+// Folded form of the staged path: binning of positions [pos0, pos0 + n_pos), then one launch that
+// images them all (`items` workgroups take one item each, a second launch loops over what is left).
+hipError_t launch_fold_bin_desc(const DescArgs& a, hipStream_t s);
+hipError_t launch_fold_desc(const DescArgs& a, int prec, unsigned items, hipStream_t s);
+
 // The staged form of the uneven-batch path (staged.hip, one object per precision): the fused
 // column kernel and the row kernel of one chunk (images of one grid size 2^logn, at most `slots`
 // of them) with strip width `strip` and `tpb` row-pair transforms.
@@ -288,6 +295,14 @@ struct DescArgs {
   int* occ;                        // [n_img] occupied cells (uniform weighting), by position
   int* ext;                        // [n_img] column extent, by position
   int col_log_strip[13];           // per log2 N: log2 of the column kernel's strip width
+  // folded form of the staged path: the images at positions [pos0, pos0 + n_pos) of the order, whose
+  // arrays are indexed by position - pos0
+  int4* sizes;                     // [13] per log2 N: {first position, images, 0, 0}; null: not the folded form
+  int pos0, n_pos, ent_stride;
+  FoldHeader* hdr;
+  uint32_t* rows;
+  uint32_t* rec;
+  float2* val;
 };
 // Staged form: the chunk table reserves, for each grid size 2^logn <= the batch's largest, the
 // chunk slots that n_img images of that size could fill (largest size first), so that the host

@@ -48,6 +48,11 @@ __global__ __launch_bounds__(1024) void k_desc_prep(DescArgs a) {
     *a.status = s_bad ? BLINK_DESC_BAD : 0;
   }
   __syncthreads();
+  if (a.sizes && tid < 10) {
+    const int b = 9 - tid;                // log2 N = tid + 3
+    a.sizes[tid + 3] = make_int4(s_bucket[b], s_bucket[b + 1] - s_bucket[b], 0, 0);
+  }
+  if (a.sizes) __syncthreads();           // before the order is written through the buckets
   if (a.chunks) {
     // Staged form: the images of one bucket (one grid size) go in chunks of as many as the chunk
     // buffer holds, in that size's reserved range of the chunk table (staged_slots); the
