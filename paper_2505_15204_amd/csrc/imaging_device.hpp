@@ -88,8 +88,10 @@ struct BinShared {
 // record {kv*N + ku, b | conj<<31}), the strip offsets off[0..ku_limit>>log_strip], the kept and
 // out-of-grid counts, and cell_idx[b] when non-null. When ext_out is non-null it receives the
 // column extent: (index of the last strip holding a placement + 1) * 2^log_strip, 0 when no
-// placement is kept; every column at or beyond it is zero in the grid. One workgroup (a multiple
-// of 64 threads, at least 512 so that the strip count fits the scan).
+// placement is kept; every column at or beyond it is zero in the grid. With ROWS the strips are
+// 2^log_strip rows instead (kv in place of ku; the whole grid, ku_limit = N). One workgroup (a
+// multiple of 64 threads, at least 512 so that the strip count fits the scan).
+template <bool ROWS = false>
 __device__ inline void bin_visibilities(const double* __restrict__ uvw, const uint8_t* __restrict__ fl, int B,
                                         double k, int logn, int log_strip, int ku_limit, int2* __restrict__ plc,
                                         int* __restrict__ off, int* kept_out, int* nout_out,
@@ -109,8 +111,9 @@ __device__ inline void bin_visibilities(const double* __restrict__ uvw, const ui
         const int ku1 = iu & mask, kv1 = iv & mask, ku2 = (-iu) & mask;
         cell = kv1 * N + ku1;
         ++kept;
-        if (ku1 < ku_limit) atomicAdd(&sh.cnt[ku1 >> log_strip], 1);
-        if (ku2 < ku_limit) atomicAdd(&sh.cnt[ku2 >> log_strip], 1);
+        const int s1 = ROWS ? kv1 : ku1, s2 = ROWS ? (-iv) & mask : ku2;
+        if (ku1 < ku_limit) atomicAdd(&sh.cnt[s1 >> log_strip], 1);
+        if (ku2 < ku_limit) atomicAdd(&sh.cnt[s2 >> log_strip], 1);
       } else {
         cell = -2;
         ++outside;
@@ -140,11 +143,11 @@ __device__ inline void bin_visibilities(const double* __restrict__ uvw, const ui
     const int ku1 = iu & mask, kv1 = iv & mask;
     const int ku2 = (-iu) & mask, kv2 = (-iv) & mask;
     if (ku1 < ku_limit) {
-      int pos = atomicAdd(&sh.cnt[ku1 >> log_strip], 1);
+      int pos = atomicAdd(&sh.cnt[(ROWS ? kv1 : ku1) >> log_strip], 1);
       plc[pos] = make_int2(kv1 * N + ku1, b);
     }
     if (ku2 < ku_limit) {
-      int pos = atomicAdd(&sh.cnt[ku2 >> log_strip], 1);
+      int pos = atomicAdd(&sh.cnt[(ROWS ? kv2 : ku2) >> log_strip], 1);
       plc[pos] = make_int2(kv2 * N + ku2, (int)((unsigned)b | 0x80000000u));
     }
   }

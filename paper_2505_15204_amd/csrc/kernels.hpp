@@ -31,9 +31,11 @@ constexpr int kTunedLogn = 8;
 template <int LOGN>
 struct GridCfg {
   static constexpr int N = 1 << LOGN;
-  static constexpr int S = pow2_floor(cmin(N, (128 * 1024) / (N * 12)));
-  static constexpr int THREADS = 256;
+  static constexpr int S = pow2_floor(cmin(N, (128 * 1024) / (N * 12)));   // rows of a strip
 };
+constexpr int kGridThreads = 512;
+constexpr int kGridPart = 4096;              // cells of a workgroup
+constexpr int kGridBatch = 4;                // records a thread loads together
 
 // A row variant fits when TPB transforms of N padded points plus the twiddle table fit in LDS.
 template <int LOGN, int TPB>
