@@ -493,32 +493,33 @@ __device__ __forceinline__ void grid_colfft_conv_task(const float2* __restrict__
 // Grid correction of one axis: corr[x] = 1 / c(X/N), X the signed offset of pixel x from the
 // phase centre (x - N/2 when shifted, else x below N/2 and x - N above), with
 // c(nu) = W * integral_0^{pi/2} exp(beta (cos t - 1)) cos(pi nu W sin t) cos t dt (the kernel's
-// transform after d = (W/2) sin t), by composite Simpson's rule on 8192 intervals in FP64.
-// One workgroup of 256 threads per pixel.
-constexpr int kCorrIntervals = 8192;
+// transform after d = (W/2) sin t), by the five-point Gauss-Legendre rule on 64 intervals in FP64.
+// The integrand is entire with derivatives of order n up to about 47^n (a Gaussian of width 0.1 at
+// beta = 100 times a cosine of frequency 8 pi at W = 16): the rule's error bound is 4e-13 h^11 47^10
+// 64 = 3e-12 at h = pi/128, far below the rounding to FP32. One workgroup per pixel, a node per
+// thread: 1024 pixels 7 us; Simpson's rule on 8192 intervals, 54 us.
+constexpr int kCorrPanels = 64, kCorrNodes = 5, kCorrThreads = kCorrPanels * kCorrNodes;
 
 __device__ inline void conv_correction_entry(float* corr, int N, int x, int width, double beta, int shift,
                                              double* s_part) {
   const int X = shift ? x - N / 2 : (x < N / 2 ? x : x - N);
   const double nu = (double)X / N;
-  const double h = (M_PI / 2.0) / kCorrIntervals;
-  double s = 0.0;
-  for (int i = threadIdx.x; i <= kCorrIntervals; i += blockDim.x) {
-    double st, ct;
-    sincos(i * h, &st, &ct);
-    const double f = exp(beta * (ct - 1.0)) * cos(M_PI * nu * width * st) * ct;
-    const double w = (i == 0 || i == kCorrIntervals) ? 1.0 : ((i & 1) ? 4.0 : 2.0);
-    s += w * f;
-  }
-  s_part[threadIdx.x] = s;
+  const double h = (M_PI / 2.0) / kCorrPanels;
+  const int tid = threadIdx.x, panel = tid % kCorrPanels, node = tid / kCorrPanels;   // one node per wave
+  // nodes 0, +- sqrt(5 -+ 2 sqrt(10/7)) / 3 of [-1, 1]; weights 128/225, (322 +- 13 sqrt 70) / 900
+  const double far = node > 2 ? 1.0 : -1.0;
+  const double z = node == 0 ? 0.0 : sqrt(5.0 + far * 2.0 * sqrt(10.0 / 7.0)) / 3.0 * (node & 1 ? 1.0 : -1.0);
+  const double w = node == 0 ? 128.0 / 225.0 : (322.0 - far * 13.0 * sqrt(70.0)) / 900.0;
+  double st, ct;
+  sincos((panel + 0.5 + 0.5 * z) * h, &st, &ct);
+  double s = w * exp(beta * (ct - 1.0)) * cos(M_PI * nu * width * st) * ct;
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+  if (panel == 0) s_part[node] = s;
   __syncthreads();
-  for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) s_part[threadIdx.x] += s_part[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const double c = (double)width * s_part[0] * h / 3.0;
-    corr[x] = (float)(1.0 / c);
+  if (tid == 0) {
+    double t = 0.0;
+    for (int i = 0; i < kCorrNodes; ++i) t += s_part[i];
+    corr[x] = (float)(1.0 / ((double)width * t * (0.5 * h)));
   }
 }
 

@@ -132,14 +132,14 @@ hipError_t launch_bin_conv(const BinArgs& a, ConvParams cp, int rec_stride, hipS
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void k_conv_correction(float* corr, int n, int width, double beta, int shift) {
-  __shared__ double s_part[256];
+__global__ __launch_bounds__(kCorrThreads) void k_conv_correction(float* corr, int n, int width, double beta, int shift) {
+  __shared__ double s_part[kCorrNodes];
   conv_correction_entry(corr, n, blockIdx.x, width, beta, shift, s_part);
 }
 
 hipError_t launch_conv_correction(float* corr, int logn, ConvParams cp, int shift, hipStream_t s) {
   const int n = 1 << logn;
-  k_conv_correction<<<n, 256, 0, s>>>(corr, n, cp.width, cp.beta, shift);
+  k_conv_correction<<<n, kCorrThreads, 0, s>>>(corr, n, cp.width, cp.beta, shift);
   return hipGetLastError();
 }
 
