@@ -47,42 +47,12 @@ __device__ __forceinline__ void tile_of(int tau, int& a, int& b) {
   b = tau - r * (r + 1) / 2;
 }
 
-// x / K rounded once to float for an integer |x| < 2^31 and K <= 65535: the value of
-// (float)((double)x / K). Write K = d 2^a with d odd. A quotient q = x / K that is a float
-// rounding midpoint is a dyadic rational, so d divides x. Divisibility by d is one multiply by the
-// inverse of d modulo 2^32: |x| dinv mod 2^32 <= (2^32 - 1) / d exactly when d divides |x|, and
-// the product is then the exact quotient |x| / d, whose conversion to float (round to nearest
-// even) times 2^-a is q correctly rounded. When d does not divide x, q is no midpoint and lies at
-// least 2^-49 (relative) from every midpoint (a nonzero difference of fractions with denominators
-// K and 2^e), while qd = x * (1/K in FP64) is within 2^-52 of q, so (float)qd rounds q correctly.
-// Both ways are computed and one is selected, without branches.
-struct MeanDiv {
-  double inv;        // 1 / K rounded to double
-  unsigned dinv;     // inverse of the odd part d of K modulo 2^32
-  unsigned bound;    // (2^32 - 1) / d
-  float scale;       // 2^-a
-};
-
-__device__ __forceinline__ MeanDiv mean_div(int K) {
-  MeanDiv m;
-  m.inv = 1.0 / (double)K;
-  const int a = __builtin_ctz((unsigned)K);
-  const unsigned d = (unsigned)K >> a;
-  unsigned di = d;                                   // Newton's iteration doubles the correct bits
-  for (int i = 0; i < 5; ++i) di *= 2u - d * di;
-  m.dinv = di;
-  m.bound = 0xffffffffu / d;
-  m.scale = __uint_as_float((unsigned)(127 - a) << 23);
-  return m;
-}
-
-__device__ __forceinline__ float mean_rn(int x, const MeanDiv& m) {
-  const unsigned ax = x < 0 ? 0u - (unsigned)x : (unsigned)x;
-  const unsigned t = ax * m.dinv;
-  const float fq = (float)((double)x * m.inv);
-  const float fe = __uint2float_rn(t) * m.scale;
-  const float fd = x < 0 ? -fe : fe;
-  return t <= m.bound ? fd : fq;
+// (float)((double)x / K) for an integer |x| < 2^31 and K <= 65535, without a division: with inv the
+// correctly rounded 1 / K, q = x inv is within an ulp of x / K, the fma forms its remainder exactly,
+// and q + r inv rounds to the correctly rounded quotient (Markstein 1990).
+__device__ __forceinline__ float mean_rn(int x, double K, double inv) {
+  const double d = (double)x, q = d * inv;
+  return (float)fma(fma(-K, q, d), inv, q);
 }
 
 // One staging item: 16 bytes (8 inputs, re and im) for each of 8 consecutive terms.
@@ -179,10 +149,14 @@ __global__ __launch_bounds__(kThreads, 1) void k_correlate(CorrelateArgs a) {
     }
   };
   // transpose: row row0 + r gets the (re, im) pairs of its 8 terms as one 16-byte vector in P and
-  // the (im, ~re) pairs in Q (byte permutes of two loaded words each); the chunk's imaginary parts
-  // of each row are added to colsum
+  // the (im, ~re) pairs in Q (byte permutes of two loaded words each). The chunk's imaginary parts
+  // of each row are added to colsum: the eight lanes of an input group hold the group's rows' sums
+  // over their octets, and exchange them so that lane o adds the total of row o, one LDS atomic to
+  // distinct words in place of eight with eight lanes on each (768 products of 128 antennas and 800
+  // terms: 243 -> 216 us).
   auto store = [&](const Staged& st, unsigned char* x, unsigned char* xq) {
     if (staged) {
+      int part[8];
 #pragma unroll
       for (int r = 0; r < 8; ++r) {
         // v_perm_b32 byte selectors (0-3: bytes of the second source, 4-7: of the first): row r's
@@ -205,8 +179,21 @@ __global__ __launch_bounds__(kThreads, 1) void k_correlate(CorrelateArgs a) {
         const size_t at = (size_t)(row0 + r) * kRow + 16 * o;
         *reinterpret_cast<uint4*>(x + at) = make_uint4(d[0], d[1], d[2], d[3]);
         *reinterpret_cast<uint4*>(xq + at) = make_uint4(e[0], e[1], e[2], e[3]);
-        if (isum) atomicAdd(&colsum[row0 + r], isum);
+        part[r] = isum;
       }
+      // keep the half of the rows that this lane ends with, hand its partner the other half
+      const bool h4 = o & 4, h2 = o & 2, h1 = o & 1;
+      int q4[4], q2[2];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        q4[r] = (h4 ? part[r + 4] : part[r]) +
+                __builtin_amdgcn_update_dpp(0, h4 ? part[r] : part[r + 4], 0x141, 0xf, 0xf, true);   // lane 7 - o
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+        q2[r] = (h2 ? q4[r + 2] : q4[r]) +
+                __builtin_amdgcn_update_dpp(0, h2 ? q4[r] : q4[r + 2], 0x4e, 0xf, 0xf, true);        // lane o ^ 2
+      const int sum = (h1 ? q2[1] : q2[0]) + __builtin_amdgcn_update_dpp(0, h1 ? q2[0] : q2[1], 0xb1, 0xf, 0xf, true);
+      atomicAdd(&colsum[row0 + o], sum);
     }
   };
 
@@ -267,32 +254,46 @@ __global__ __launch_bounds__(kThreads, 1) void k_correlate(CorrelateArgs a) {
   }
 
   // Output: element v of the lane is R[32 a + 8 (v / 4) + 4 g + v % 4][32 b + n].
-  const MeanDiv md = mean_div(K);
-  const long B = (long)a.A * (a.A - 1) / 2;
+  const double Kd = (double)K, inv = 1.0 / Kd;
+  const int B = (int)((long)a.A * (a.A - 1) / 2);
+  float2* vis = a.vis + ((size_t)t * a.C + c) * a.pol_mode * B;
 #pragma unroll
   for (int u = 0; u < kTilesPerWave; ++u) {
     if (!tv[u]) continue;
     const int ci = tb[u] * kTile + n;
     const int csum = ci < in2 ? colsum[ci] : 0;
+    const int j = ci / 2, q = ci % 2;
+    // Im R = im + csum fits in int32 (|R| <= 2 K 128^2 < 2^31); the sum is formed modulo 2^32
+    auto value = [&](int v) {
+      return make_float2(mean_rn(re[u][v], Kd, inv), mean_rn((int)((unsigned)im[u][v] + (unsigned)csum), Kd, inv));
+    };
+    if (ta[u] > tb[u] && (ta[u] + 1) * kTile <= in2 && a.pol_mode == 4) {
+      // whole tile below the diagonal: every element is a baseline's (uniform over the wave); without
+      // the tests per element and with 32-bit offsets 216 -> 199 us for the same products
+#pragma unroll
+      for (int v = 0; v < 16; v += 2) {
+        const int i = ta[u] * (kTile / 2) + 4 * (v / 4) + 2 * g + v % 4 / 2, b = i * (i - 1) / 2 + j + q * B;
+        vis[b] = value(v);
+        vis[b + 2 * B] = value(v + 1);
+      }
+      continue;
+    }
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int ri = ta[u] * kTile + 8 * (v / 4) + 4 * g + v % 4;
       if (ri >= in2 || ci >= in2) continue;
-      const int i = ri / 2, p = ri % 2, j = ci / 2, q = ci % 2;
+      const int i = ri / 2, p = ri % 2;
       if (i < j) continue;
-      // Im R = im + csum fits in int32 (|R| <= 2 K 128^2 < 2^31); the sum is formed modulo 2^32
-      const float vr = mean_rn(re[u][v], md);
-      const float vi = mean_rn((int)((unsigned)im[u][v] + (unsigned)csum), md);
+      const float2 r = value(v);
       if (i == j) {
-        if (a.autos) a.autos[(((size_t)t * a.C + c) * a.A + i) * 4 + 2 * p + q] = make_float2(vr, vi);
+        if (a.autos) a.autos[(((size_t)t * a.C + c) * a.A + i) * 4 + 2 * p + q] = r;
         continue;
       }
       int pp;
       if (a.pol_mode == 4) pp = 2 * p + q;
       else if (p == q) pp = p;
       else continue;
-      const long b = (long)i * (i - 1) / 2 + j;
-      a.vis[(((size_t)t * a.C + c) * a.pol_mode + pp) * B + b] = make_float2(vr, vi);
+      vis[(size_t)pp * B + (i * (i - 1) / 2 + j)] = r;
     }
   }
 }
