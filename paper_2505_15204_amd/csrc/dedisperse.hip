@@ -15,6 +15,7 @@ constexpr int kPx = 64;                          // pixels of a workgroup, one p
 constexpr int kStage = 4;                        // channels per LDS stage
 constexpr int kMaxRows = 60;                     // time steps of one channel in a stage
 constexpr int kMaxChannels = 4096;               // row ranges kept in the LDS
+constexpr int kMinReads2 = 5;                    // twice the reads per copied step that the tiled form needs
 constexpr int kMinGroups = 96;                   // workgroups below which the tiled form is not taken
 
 // One output value per thread and pixel quad, every input read where it is used: for the shapes
@@ -209,7 +210,12 @@ hipError_t launch_dedisperse(const float* in, int C, int logn, const int* delays
   // pixels x 768 channels x 16 trials (256 workgroups) take 0.73 ms tiled and 2.6 ms untiled, 64^2
   // (64 workgroups) 0.57 and 0.43 ms.
   const int nk = (n_dm + kDms - 1) / kDms;
-  bool fits = C <= kMaxChannels && g.groups <= 4096 && nn / kPx * g.groups >= kMinGroups;
+  // The steps copied to LDS have to be read often enough, by enough of the workgroup's waves: 3 trials
+  // to a large DM (100 channels of 256^2, 30 steps) read each copied step 1.4 times and take 292 us tiled
+  // and 140 untiled; 2 trials to a small one 1.9 times, 201 and 218 us; 8 trials of 60 channels of 128^2 63
+  // and 117.
+  long copied = 0;
+  bool fits = C <= kMaxChannels && g.groups <= 4096 && nn / kPx * g.groups >= kMinGroups && g.units >= kWaves / 2;
   for (int c = 0; fits && c < C; ++c) {
     for (int q = 0; q < g.groups; ++q) {
       const int u0 = q * kWaves, u1 = u0 + kWaves < g.units ? u0 + kWaves : g.units;
@@ -224,9 +230,11 @@ hipError_t launch_dedisperse(const float* in, int C, int logn, const int* delays
         }
       }
       g.rows = hi - lo > g.rows ? hi - lo : g.rows;
+      copied += hi - lo;
     }
     fits = g.rows <= kMaxRows;
   }
+  fits = fits && 2 * (long)n_dm * t_out * C >= kMinReads2 * copied;
   if (fits) return launch_tile<kMaxTb>(g.tb, in, C, 2 * logn, delays, n_dm, t_out, g, out, s);
   const long nn4 = nn / 4;
   dim3 grid((unsigned)((nn4 + 255) / 256), (unsigned)t_out, (unsigned)n_dm);
