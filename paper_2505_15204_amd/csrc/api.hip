@@ -664,12 +664,17 @@ static blink_status image_batch(blink_ctx ctx, const blink_cf32* vis, const uint
     KernelTimer kt(ctx, BLINK_KERNEL_CORRECT, s);
     return blink::launch_correct_vis(xa, s);
   };
-  // The folded path takes every size and baseline count that its layout holds: it was faster than
-  // the two-pass form below at all of them (64 images of 1024^2: 121 against 225 us per call; 1536:
-  // 2.34 against 4.10 ms; 16 of 4096^2 in the split FP16 form: 0.50 against 1.30 ms; 130 of 512^2
-  // with corrections: 87 against 163 us; one of 256^2: 43 against 49 us). The two-pass form serves
-  // smaller grids, larger arrays and workspaces that do not hold one pair's placement lists.
-  if (logn >= blink::kFoldMinLogn && B > 0 && B <= blink::kFoldMaxB) {
+  // The folded path takes the sizes and baseline counts that its layout holds from 512^2 on: it is
+  // faster than the two-pass form below at all of them (64 images of 1024^2: 121 against 225 us per call;
+  // 1536: 2.34 against 4.10 ms; 16 of 4096^2 in the split FP16 form: 0.50 against 1.30 ms; 130 of 512^2
+  // with corrections: 87 against 163 us; one of 512^2 with 276 baselines: 29.5 against 30.3 us). At 256^2
+  // its binning takes longer than it saves for few images of few baselines (630 baselines: 1 image 29
+  // against 21 us, 18 images 30 against 24, 300 images 65 against 70; 8128 baselines: 1 image 43
+  // against 49), and up to 128^2 it always does (600 images, 8128 baselines: 120 against 108 us; 300,
+  // 10296 baselines: 105 against 84). The two-pass form serves those, larger arrays and workspaces
+  // that do not hold one pair's placement lists.
+  const bool folds = logn > 8 || (logn == 8 && (B >= 4096 || n_tc * P >= 192));
+  if (folds && B > 0 && B <= blink::kFoldMaxB) {
     const int m = blink::fold_rows(logn);
     const size_t Q = largest_fitting_chunk(n_tc, workspace_bytes,
                                            [&](size_t q) { return fold_layout(q, P, B, corrected).total; });
@@ -1350,8 +1355,9 @@ blink_status run_desc_folded(blink_ctx ctx, const DescCall& c, int max_logn, siz
     const int64_t most = (int64_t)a.n_pos * ((1 << max_logn) / blink::fold_rows(max_logn)) + 80;
     int64_t items = c.images_len / (2 * blink::kFoldCells) + a.n_pos + 80;
     if (items > most) items = most;
+    if (items > (1 << 22)) items = 1 << 22;      // (an images_len beyond the array; grids stay below 2^32 threads)
     KernelTimer kt(ctx, BLINK_KERNEL_GRID_COLFFT, s);
-    e = blink::launch_fold_desc(a, c.precision, (unsigned)(items < 0x7fffffff ? items : 0x7fffffff), s);
+    e = blink::launch_fold_desc(a, c.precision, (unsigned)items, s);
   }
   if (e != hipSuccess) return hip_fail(ctx, e, "uneven-batch folded kernels");
   return BLINK_OK;

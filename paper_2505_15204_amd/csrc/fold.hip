@@ -137,8 +137,6 @@ hipError_t FoldLaunch<PREC>::image(const FoldArgs& a, const float2* tw, hipStrea
   if (a.n_img <= 0) return hipSuccess;
   using F = FoldFor<PREC>;
   switch (a.logn) {
-    case 6: return F::template size<6>(a, tw, s);
-    case 7: return F::template size<7>(a, tw, s);
     case 8: return F::template size<8>(a, tw, s);
     case 9: return F::template size<9>(a, tw, s);
     case 10: return F::template size<10>(a, tw, s);

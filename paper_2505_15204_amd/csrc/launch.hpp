@@ -101,7 +101,6 @@ hipError_t launch_row_c2r(const RowArgs& a, int n_img, int tpb, int prec, const 
 struct DescArgs;
 constexpr int kFoldDiag = 16;              // placements of a segment stored in the jagged diagonals
 constexpr int kFoldCells = 8192;           // most folded cells (M N / 2) of a class
-constexpr int kFoldMinLogn = 6;            // smallest grid that blink_image_batch images this way
 constexpr int kFoldMaxB = 16 * 1024;       // baselines a binning workgroup keeps in registers
 // Rows of a residue class: M N = 16384 (two classes fill the LDS of one compute unit), at most the
 // whole grid.
