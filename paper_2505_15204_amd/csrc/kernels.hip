@@ -284,6 +284,27 @@ __global__ __launch_bounds__(64 * SLICES * WIDTH) void k_image_average(const f32
   if (px < nn4) out[img * nn4 + px] = f32x4{(float)(a[0] * inv), (float)(a[1] * inv), (float)(a[2] * inv), (float)(a[3] * inv)};
 }
 
+// One thread per pixel quad and output, every input through the caches: for one output of few inputs.
+__global__ __launch_bounds__(256) void k_image_average_few(const f32x4* __restrict__ in, int C, int P, long nn4,
+                                                           int axes, int Co, int Po, long n_quads, AvgRuns r,
+                                                           f32x4* __restrict__ out) {
+  const long gid = (long)blockIdx.x * 256 + threadIdx.x;
+  if (gid >= n_quads) return;
+  const long img = gid / nn4, px = gid - img * nn4;
+  const int po = (int)(img % Po), co = (int)((img / Po) % Co), to = (int)(img / ((long)Po * Co));
+  const long first = ((long)((axes & 1) ? 0 : to) * C + ((axes & 2) ? 0 : co)) * P + ((axes & 4) ? 0 : po);
+  const f32x4* src = in + first * nn4 + px;
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int i = 0; i < r.n2; ++i)
+    for (int j = 0; j < r.n1; ++j) {
+      const f32x4 v = src[(i * r.s2 + j * r.s1) * nn4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a[q] += (double)v[q];
+    }
+  const double inv = 1.0 / ((double)r.n1 * r.n2);
+  out[gid] = f32x4{(float)(a[0] * inv), (float)(a[1] * inv), (float)(a[2] * inv), (float)(a[3] * inv)};
+}
+
 hipError_t launch_image_average(const float* in, int T, int C, int P, int logn, int axes, float* out, hipStream_t s) {
   const long nn4 = (1L << (2 * logn)) / 4;
   const int To = (axes & 1) ? 1 : T, Co = (axes & 2) ? 1 : C, Po = (axes & 4) ? 1 : P;
@@ -306,11 +327,16 @@ hipError_t launch_image_average(const float* in, int T, int C, int P, int logn, 
   f32x4* dst = (f32x4*)out;
   auto blocks = [&](int width) { return (unsigned)((nn4 + 64 * width - 1) / (64 * width) * n_img); };
   if ((nn4 + 63) / 64 * n_img > 0x7fffffffL) return hipErrorInvalidValue;
-  // Below 16 inputs the sum is short; below 2048 blocks of 256 pixels (256^2 and smaller, one output)
+  // Below 16 inputs the sum is short, and it is below 64 where the pixels alone fill the chip: there
+  // plain loads with a thread per pixel quad (40 inputs of 2048^2: 119 us, 126 with 8 slices; 3 inputs: 11.6
+  // and 13.4) unless there are many outputs (80 of 2 inputs of 1024^2: 155 us against 167 plain). 84
+  // inputs of 2048^2 take 235 us with 8 slices, 250 plain. Below 2048 blocks of 256 pixels (256^2 and smaller, one output)
   // more waves per output are needed than the 8 slices of the wider form give: 8400 images of
   // 256^2 take 337 us with 16 slices, 3886 us with one; 1536 of 1024^2 1055 us with 8 slices of 512
   // pixels, 1078 with 4 of 256, 1228 with 4 of 1024, 1211 with one (one thread per pixel quad).
-  if (n < 16) k_image_average<1, 1><<<blocks(1), 64, 0, s>>>(src, C, P, nn4, axes, Co, Po, r, dst);
+  if (n < 16 ? n_img == 1 : n < 64 && blocks(1) >= 2048)
+    k_image_average_few<<<blocks(4), 256, 0, s>>>(src, C, P, nn4, axes, Co, Po, nn4 * n_img, r, dst);
+  else if (n < 16) k_image_average<1, 1><<<blocks(1), 64, 0, s>>>(src, C, P, nn4, axes, Co, Po, r, dst);
   else if (blocks(1) >= 2048) k_image_average<8, 2><<<blocks(2), 1024, 0, s>>>(src, C, P, nn4, axes, Co, Po, r, dst);
   else k_image_average<16, 1><<<blocks(1), 1024, 0, s>>>(src, C, P, nn4, axes, Co, Po, r, dst);
   return hipGetLastError();
