@@ -92,34 +92,29 @@ def column_extent(torch, d, spec, steps):
     return sum(per_t[i % spec.T] for i in range(steps)) / steps
 
 
-def kernel_unit_bytes(spec, ext=None):
-    """Algorithmic HBM bytes per unit of work of each kernel (unit, bytes).
+def kernel_unit_bytes(spec):
+    """Algorithmic HBM bytes per unit of work of the folded path's kernels (unit, bytes).
 
-    `ext` is the mean number of half-spectrum columns that carry data per image (column_extent);
-    None means all N/2 (paths that transform every column).
-    grid_colfft: per image, write the nonzero columns of the half-spectrum intermediate (N rows x
-                 ext columns of complex64, 8 N ext B; 4 N^2 B with every column) and read each
-                 visibility once (8 B) plus its placement record (8 B).
-    row_fft:     per image, read those columns (8 N ext B) and write the FP32 image (4 N^2 B).
-    bin:         per (t,c) pair, read the flag (1 B) of each baseline and write at most one
-                 placement record (8 B) per baseline (one per kept visibility in the half plane,
-                 two for the few on the u = 0 column); u, v (16 B per baseline) are shared by the
-                 C channels of a time step, so each pair is charged 16 B / C of them.
+    bin:         per (t,c) pair, read the flag (1 B) of each baseline and the visibility (8 B) of each
+                 baseline and polarisation, write one placement record (4 B) per baseline and one
+                 value (8 B) per baseline and polarisation (one placement per kept visibility in the
+                 half plane, two for the few on the u = 0 column); u, v (16 B per baseline) are shared
+                 by the C channels of a time step, so each pair is charged 16 B / C of them.
+    grid_colfft: (the folded imaging kernel) per image, read each value once and the pair's records
+                 (4 B per baseline, shared by the polarisations) and write the FP32 image (4 N^2 B).
     """
-    N, B, C = spec.grid_n, spec.B, spec.C
-    h = 8 * N * (N / 2 if ext is None else ext)
+    N, B, C, P = spec.grid_n, spec.B, spec.C, spec.P
     return {
-        "grid_colfft": ("image", round(h + 16 * B)),
-        "row_fft": ("image", round(h + 4 * N * N)),
-        "bin": ("pair", 9 * B + (16 * B) // C),
+        "grid_colfft": ("image", 4 * N * N + 8 * B + 4 * B // P),
+        "bin": ("pair", B + (16 * B) // C + 4 * B + 16 * B * P),
     }
 
 
-def path_bytes_per_image(spec, ext=None):
-    """The whole path per image: write and read the nonzero half-spectrum columns, write the image,
-    read the visibilities and placements and the per-pair binning bytes shared by the pols."""
-    N, B, P = spec.grid_n, spec.B, spec.P
-    return round(16 * N * (N / 2 if ext is None else ext) + 4 * N * N + 8 * B + B // P)
+def path_bytes_per_image(spec):
+    """The whole path per image: write the image, read the visibility, write and read its value, and the
+    per-pair bytes shared by the pols (flags, u and v, the records written and read)."""
+    N, B, C, P = spec.grid_n, spec.B, spec.C, spec.P
+    return round(4 * N * N + 24 * B + (9 * B + 16 * B / C) / P)
 
 
 def conv_unit_bytes(torch, d, spec, width, steps, strip=16, band=16):
@@ -180,10 +175,6 @@ def conv_unit_bytes(torch, d, spec, width, steps, strip=16, band=16):
         "row_fft": ("image", round(hb + 4 * N * N)),
         "bin": ("pair", round(B + (16 * B) // C + 16 * R + 4 * (nstrips * nbands + 1))),
     }, ext
-
-
-# The last-level cache (AMD Infinity Cache, "MALL") of the MI355X: 256 MB in front of HBM.
-MALL_BYTES = 256 * 10**6
 
 
 def cpu_baseline(d, spec, budget_s):
@@ -415,9 +406,9 @@ def bench_phase2(ctx, torch, blink, synth, steps, warmup):
     n_img = steps * C * P
     value = n_img / (ms / 1e3)
     prof, _ = profiled(ctx, torch, step, 1)
-    kernels = kernel_table(prof, {"image": C * P, "pair": C}, kernel_unit_bytes(spec, column_extent(torch, d, spec, 1)))
+    kernels = kernel_table(prof, {"image": C * P, "pair": C}, kernel_unit_bytes(spec))
     ext = column_extent(torch, d, spec, steps)
-    per_image = path_bytes_per_image(spec, ext)
+    per_image = path_bytes_per_image(spec)
     out = {"workload": "phase2-2048: 144 tiles (10296 cross baselines), 2 pols, 3072 x 10 kHz channels from 185 MHz, "
                        "20 x 1 ms time steps, 2048^2 FP32 grid, 0.75 arcmin pixels, uniform weighting, 10% flags; "
                        "one step = one time step = 6144 images in 4 calls of 768 channels",
@@ -451,23 +442,13 @@ def bench_uneven(ctx, torch, blink, synth, reps, desc_form="auto"):
     n_img = lay["n_img"]
     ws = torch.empty(blink.desc_workspace_size(n_img, lay["max_b"], lay["max_n"], 1024), dtype=torch.uint8,
                      device=dev)
-    # per image: the nonzero half-spectrum columns written and read back (16 N E), the image
-    # (4 N^2) and 9 B per baseline; E = 1 + the largest |ku| over the image's baselines (none is
-    # flagged in this batch)
-    ext = []
-    for i in range(n_img):
-        n, o, nb = int(lay["grid_n"][i]), int(lay["uvw_offset"][i]), int(lay["n_baselines"][i])
-        k = lay["freq_hz"][i] / SPEED_OF_LIGHT * n * lay["pixel_scale"][i]
-        u = np.rint(lay["uvw_ext"][o:o + nb, :2] * k)
-        keep = (np.abs(u) < n / 2).all(axis=1)
-        ext.append(int(np.abs(u[keep, 0]).max()) + 1 if keep.any() else 0)
-    model = int(sum(16 * int(n) * e + 4 * int(n) ** 2 + 9 * int(b)
-                    for n, e, b in zip(lay["grid_n"], ext, lay["n_baselines"])))
+    # per image: the image (4 N^2) and 40 B per baseline (u, v and the visibility read, the placement's
+    # record and value written and read)
+    model = int(sum(4 * int(n) ** 2 + 40 * int(b) for n, b in zip(lay["grid_n"], lay["n_baselines"])))
     sizes = {int(n): int((lay["grid_n"] == n).sum()) for n in sorted(set(lay["grid_n"].tolist()))}
     out = {"workload": "uneven: 4096 images, f = 70-300 MHz, N = 512 / 1024 / 2048 below 120 / 200 MHz / above, "
                        "pixel scale per channel so every baseline fits, 70-100% of 8128 baselines per image",
-           "images": n_img, "images_per_size": sizes, "bytes_model_total": model,
-           "column_extent_mean_fraction": round(float(np.mean([e / (n / 2) for e, n in zip(ext, lay["grid_n"])])), 3)}
+           "images": n_img, "images_per_size": sizes, "bytes_model_total": model}
     for name, prec in FORMS:
         if desc_form == "auto":
             # the descriptor autotuner picks the form (staged or persistent) and the persistent form's block
@@ -518,8 +499,8 @@ def main():
                     help="form of the uneven batch: auto runs the descriptor autotuner per precision (default); "
                          "staged or persistent fix the form with its default plan (for profiles)")
     ap.add_argument("--no-cache-probe", action="store_true",
-                    help="skip the pass with image groups whose half spectra exceed the last-level cache (profiles "
-                         "of the headline kernels use it so that every traced launch has the headline plan)")
+                    help="accepted for older command lines: the pass with image groups beyond the last-level cache "
+                         "went with the half spectra in memory")
     ap.add_argument("--forms", default="all",
                     help="comma-separated subset of the forms measured beside the headline: split, conv, "
                          "corrected, average, correlator, dedispersion, precision, uneven, phase2 (default all)")
@@ -606,42 +587,13 @@ def main():
     prof, prof_ms = profiled(ctx, torch, step, args.steps)
     units = {"image": n_images, "pair": args.steps * C}
     ext = column_extent(torch, d, spec, args.steps)
-    ub = kernel_unit_bytes(spec, ext)
+    ub = kernel_unit_bytes(spec)
     kernels = kernel_table(prof, units, ub)
     dom = max((k for k in kernels if k in ub), key=lambda k: kernels[k]["total_ms"])
     roof = {"kernel": dom, "bound": "hbm", "achieved": kernels[dom]["achieved_GB_s"], "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": kernels[dom]["frac_hbm"],
             "traffic": counter_traffic("vcs1024_fp32", dom, plan)}
-    # The half spectra of one image group (group x 4 N^2 bytes) are written by the column launch and
-    # read by the row launch; when they fit the 256 MB last-level cache they are served from it, and
-    # the byte counters (which sit above that cache) count those hits as HBM traffic. The same steps
-    # with a group whose half spectra exceed the cache give the kernels' rates from DRAM.
-    h_image = 8 * N * ext           # the half-spectrum columns one image writes and reads back (mean)
-    h_group = plan["group"] * h_image
-    big = 0 if args.no_cache_probe else max(plan["group"], 1)
-    while big and big * h_image <= 1.5 * MALL_BYTES:
-        big += max(plan["group"], 1)
-    if big:
-        ctx.set_plan(N, 0, plan["col_strip"], plan["row_block"], big, col_loop=plan["col_loop"])
-        bprof, bms = profiled(ctx, torch, step, min(args.steps, 10))
-        ctx.set_plan(N, 0, plan["col_strip"], plan["row_block"], plan["group"], col_loop=plan["col_loop"])
-        bk = kernel_table(bprof, {"image": min(args.steps, 10) * C * P, "pair": min(args.steps, 10) * C},
-                          kernel_unit_bytes(spec, column_extent(torch, d, spec, min(args.steps, 10))))
-    else:
-        bk, bms = {}, float("nan")
-    roof["last_level_cache"] = {
-        "note": f"a group's half spectra ({plan['group']} images x {h_image / 2**20:.2f} MiB of nonzero columns = "
-                f"{h_group / 2**20:.0f} MiB) fit the {MALL_BYTES // 10**6} MB Infinity Cache between the column and "
-                f"the row launch; the byte counters count its hits, so this fraction includes reads served from "
-                f"that cache",
-        "group_beyond_cache": big,
-        "half_spectra_MiB": round(big * h_image / 2**20),
-        "frac_hbm": {k: bk[k]["frac_hbm"] for k in ("grid_colfft", "row_fft") if k in bk},
-        "images_per_s": round(min(args.steps, 10) * C * P / (bms / 1e3), 1) if big else None}
-    log(f"groups of {big} (half spectra beyond the cache): row kernel at "
-        f"{bk.get('row_fft', {}).get('frac_hbm', 0):.3f} of HBM, column kernel at "
-        f"{bk.get('grid_colfft', {}).get('frac_hbm', 0):.3f}")
-    per_image = path_bytes_per_image(spec, ext)
+    per_image = path_bytes_per_image(spec)
     path = {"bytes_per_image_model": per_image,
             "column_extent": {"mean_columns": round(ext, 1), "of": N // 2},
             "achieved_GB_s": round(value * per_image / 1e9, 1),
@@ -669,7 +621,7 @@ def main():
                 ms = timed(torch, fstep, fs, 2)
                 fprof, _ = profiled(ctx, torch, fstep, fs)
                 fk = kernel_table(fprof, {"image": fs * C * P, "pair": fs * C},
-                                  kernel_unit_bytes(spec, column_extent(torch, d, spec, fs)))
+                                  kernel_unit_bytes(spec))
                 v = fs * C * P / (ms / 1e3)
                 forms["vcs-1024"][name] = {"images_per_s": round(v, 1), "vs_fp32": round(v / value, 4),
                                            "plan": ctx.get_plan(N, 0, prec),
@@ -713,7 +665,7 @@ def main():
                                                 out=images, weight_sum=wsum, n_out=nout, workspace=xws)
             ms = timed(torch, xstep, fs, 2)
             xprof, _ = profiled(ctx, torch, xstep, fs)
-            xub = dict(kernel_unit_bytes(spec, column_extent(torch, d, spec, fs)),
+            xub = dict(kernel_unit_bytes(spec),
                        correct=("pair", P * B * 16 + 24 * B // C + P * spec.n_tiles * 8))
             xk = kernel_table(xprof, {"image": fs * C * P, "pair": fs * C}, xub)
             v = fs * C * P / (ms / 1e3)

@@ -317,11 +317,13 @@ blink_status blink_dedisperse(blink_ctx ctx, const float *images, int T, int C, 
  *   BLINK_DESC_PERSISTENT  one persistent fused kernel whose workgroups claim images from a queue
  *                          and image each one alone (binning, gridding + column FFT, row FFT)
  *                          through a per-workgroup intermediate slot;
- *   BLINK_DESC_STAGED      one launch bins every image; then, per chunk of images of one grid size
- *                          whose half spectra fit a 256 MiB buffer (sized for the last-level
- *                          cache), a column launch and a row launch of blink_image_batch's fused
- *                          column and row kernels for that size, reading each image's visibilities
- *                          and output offset from its descriptor.
+ *   BLINK_DESC_STAGED      one launch bins every image and one images them all, the folded form of
+ *                          blink_image_batch for every size (for as many images at a time as the
+ *                          workspace holds). With more than 16384 baselines in an image, or a
+ *                          workspace that holds fewer than 64 images: per chunk of images of one grid
+ *                          size whose half spectra fit a 256 MiB buffer (sized for the last-level
+ *                          cache), a column launch and a row launch of the two-pass kernels for
+ *                          that size.
  * In both, workgroups never wait for each other (the staged launches are ordered by the stream). */
 #define BLINK_DESC_PERSISTENT 0
 #define BLINK_DESC_STAGED 1
@@ -370,8 +372,8 @@ blink_status blink_image_batch_desc(blink_ctx ctx, const blink_image_desc *desc,
 blink_status blink_get_desc_plan(blink_ctx ctx, int *block_threads, int *workgroups);
 blink_status blink_set_desc_plan(blink_ctx ctx, int block_threads, int workgroups);
 /* Descriptor-path form: BLINK_DESC_STAGED (the default) or BLINK_DESC_PERSISTENT. The staged form
- * takes each grid size's execution plan of blink_image_batch (strip width, strips per workgroup,
- * row block); block_threads and workgroups apply to the persistent form. */
+ * takes, where it works in chunks, each grid size's execution plan of blink_image_batch (strip width,
+ * strips per workgroup, row block); block_threads and workgroups apply to the persistent form. */
 blink_status blink_get_desc_form(blink_ctx ctx, int *form);
 blink_status blink_set_desc_form(blink_ctx ctx, int form);
 
@@ -405,6 +407,10 @@ blink_status blink_graph_destroy(blink_graph graph);
  * Not part of the method: how blink_image_batch schedules its kernels for one grid size,
  * weighting and precision form (each has its own plan; blink_ifft2d uses the row_block of the
  * natural-weighting plan of its precision). A plan never changes results beyond rounding order.
+ * Plans steer the two-pass form: blink_image_batch and its variants use it for grids below 256 (and
+ * small calls at 256), above 16384 baselines and in workspaces too small for the folded form, which
+ * has no options;
+ * blink_ifft2d and blink_image_batch_conv always do.
  * Fields:
  *   col_strip  columns of the half spectrum per workgroup of the fused gridding + column FFT kernel
  *   row_block  row-pair transforms per workgroup of the row FFT kernel
@@ -450,7 +456,7 @@ blink_status blink_autotune_image_batch(blink_ctx ctx, const blink_cf32 *vis, co
 enum {
     BLINK_KERNEL_BIN = 0,          /* cell indices + strip binning, one workgroup per (t, c) */
     BLINK_KERNEL_GRID = 1,         /* full-grid gridding (blink_grid) */
-    BLINK_KERNEL_GRID_COLFFT = 2,  /* fused gridding + column FFT (blink_image_batch) */
+    BLINK_KERNEL_GRID_COLFFT = 2,  /* blink_image_batch: folded imaging kernel, or gridding + column FFT */
     BLINK_KERNEL_DENSE_COLFFT = 3, /* column FFT of dense grids (blink_ifft2d) */
     BLINK_KERNEL_WEIGHTS = 4,      /* per-image 1/W */
     BLINK_KERNEL_ROW_FFT = 5,      /* row FFT, real part, 1/W, image store */

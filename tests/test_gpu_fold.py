@@ -1,4 +1,4 @@
-"""GPU parity of the folded path of blink_image_batch (64 <= N <= 4096, up to 16384 baselines) at the
+"""GPU parity of blink_image_batch on both sides of its folded path (N >= 256, up to 16384 baselines) at the
 edges of its layout: every grid size, one baseline, 64-segment rows and their remainders, image
 counts around the groups of eight, placements that pile up on one cell beyond the diagonals, the
 u = 0 column with its mirrored placements, and the baseline counts on both sides of the path's
@@ -98,6 +98,7 @@ def test_every_size(torch, ctx, N, weighting, prec):
 @pytest.mark.parametrize("B", [1, 2, 63, 64, 65, 1023, 1025])
 def test_row_remainders(torch, ctx, B):
     check(torch, ctx, "uniform", B, 256, 0, 0, shift=B % 2 == 0)
+    check(torch, ctx, "uniform", B, 512, 0, 0, shift=B % 2 == 0)
 
 
 @pytest.mark.parametrize("weighting", [0, 1])
@@ -112,11 +113,19 @@ def test_crowded_cells(torch, ctx, kind, B, N, weighting):
 def test_baseline_limits(torch, ctx, B, weighting):
     check(torch, ctx, "uniform", B, 128, weighting, 0)
     check(torch, ctx, "column0", B, 128, weighting, 0)
+    check(torch, ctx, "uniform", B, 256, weighting, 0)
+    check(torch, ctx, "column0", B, 256, weighting, 0)
 
 
 @pytest.mark.parametrize("C", [7, 8, 9, 17])
 def test_image_counts(torch, ctx, C):
     check(torch, ctx, "uniform", 100, 128, 0, 0, C=C, P=1)
+    check(torch, ctx, "uniform", 100, 512, 0, 0, C=C, P=1)
+
+
+@pytest.mark.parametrize("B,C", [(4095, 1), (4096, 1), (300, 191), (300, 192)])
+def test_rule_at_256(torch, ctx, B, C):
+    check(torch, ctx, "uniform", B, 256, 0, 0, C=C)
 
 
 def test_everything_flagged(torch, ctx):
