@@ -109,10 +109,12 @@ constexpr int fold_rows(int logn) { return logn <= 7 ? 1 << logn : kFoldCells * 
 // Row table of a pair: for each of up to 8 waves of the imaging workgroup, its rows (64 segments of
 // one diagonal) as first placement | flags, padded with empty rows to whole batches, at least two.
 constexpr int kFoldRowBatch = 8;           // rows of a wave whose loads are issued together
+constexpr int kFoldOver = 8;               // placements beyond the diagonals that a lane sums up in long lists
 constexpr int kFoldRowsPerWave = 256, kFoldRows = 8 * kFoldRowsPerWave;
 constexpr uint32_t kFoldRowFirst = 1u << 24, kFoldRowLast = 1u << 25;
-// Placements of a pair, with the diagonals padded to whole rows.
+// Placements of a pair, with the diagonals padded to whole rows (less than 64 - 1 each) and the rest to vectors.
 constexpr int fold_entries(int B) { return 2 * B + 64 * kFoldDiag; }
+static_assert(kFoldOver <= kFoldDiag, "the last vector of a list ends in the array");
 
 struct FoldHeader {                        // one (time, channel) pair
   int rows[8];                             // rows of each wave
