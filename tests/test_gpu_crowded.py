@@ -127,7 +127,7 @@ def call_us(torch, ctx, cells, N, C, weighting):
     return best
 
 
-@pytest.mark.parametrize("weighting", [0])
+@pytest.mark.parametrize("weighting", [0, 1])
 @pytest.mark.parametrize("N,C", [(1024, 64), (2048, 16)])
 def test_a_pile_costs_no_more_than_twice_a_spread_coverage(torch, ctx, N, C, weighting):
     print(f"[gpu-case] crowded timing N={N} w={weighting}", flush=True)
