@@ -44,17 +44,16 @@ __global__ __launch_bounds__((M << LOGN) >> 5, 4) void k_fold_image(FoldArgs a, 
   im.rec = a.rec + (size_t)pair * a.ent_stride;
   im.val = a.val + (size_t)img * a.ent_stride;
   im.out = a.images + (size_t)img * N * N;
-  fold_class<LOGN, M, PREC, ((M << LOGN) >> 5)>(im, r, sbuf, s_w, tw, lin, SplitCtx{&s_max, a.dft_ops});
+  fold_class<LOGN, M, PREC, ((M << LOGN) >> 5)>(im, r, threadIdx.x, sbuf, s_w, tw, lin, SplitCtx{&s_max, a.dft_ops});
 }
 
 // ---------------------------------------------------------------- uneven batches
 // One launch images every grid size of an uneven batch. Its items are the classes of the images at
 // positions [pos0, pos0 + n_pos) of the order, the largest size first, each size's count rounded up
-// to a multiple of 8; every size takes 512 threads and about 70 KB of LDS, so that the kernel's
+// to a multiple of 8; every size takes 512 threads and 68 to 76 KB of LDS, so that the kernel's
 // resources fit all of them. The host knows only that images which do not overlap have at most
 // images_len / 16384 + n_pos items and launches that many workgroups; should descriptors share
-// pixels there can be more, which a second launch (LOOP) takes in turn. That form keeps what does
-// not change over its items in registers and spills, which is why the first launch does not loop.
+// pixels there can be more, which a second launch (LOOP) takes in turn.
 // 400 images of 512^2 to 2048^2 (3.6 GB of pixels): 2721 us with the half spectra in memory (chunks
 // of one size, a column and a row launch each), 1500 us folded.
 constexpr int kDescBlock = 512;
@@ -64,7 +63,7 @@ constexpr int fold_lds() {
 }
 
 template <int LOGN, int PREC>
-__device__ __forceinline__ void fold_desc_item(const DescArgs& a, int first, int count, unsigned w, float2* lds,
+__device__ __forceinline__ void fold_desc_item(const DescArgs& a, int first, int count, unsigned w, int tid, float2* lds,
                                                unsigned* s_max) {
   constexpr int M = fold_rows(LOGN), R = (1 << LOGN) / M;
   int k, r;
@@ -72,14 +71,14 @@ __device__ __forceinline__ void fold_desc_item(const DescArgs& a, int first, int
   if (k >= count) return;                          // padding of the size's items
   const int q = first + k, at = q - a.pos0, img = a.order[q];
   const FoldHeader* h = a.hdr + at;
-  if (a.weight_sum && r == 0 && threadIdx.x == 0) a.weight_sum[img] = a.weighting ? (double)h->occ : 2.0 * (double)h->kept;
+  if (a.weight_sum && r == 0 && tid == 0) a.weight_sum[img] = a.weighting ? (double)h->occ : 2.0 * (double)h->kept;
   FoldImage im;
   im.hdr = h;
   im.rows = a.rows + (size_t)at * kFoldRows;
   im.rec = a.rec + (size_t)at * a.ent_stride;
   im.val = a.val + (size_t)at * a.ent_stride;
   im.out = a.images + a.desc[img].image_offset;
-  fold_class<LOGN, M, PREC, kDescBlock>(im, r, lds, lds + (M / 2) * FftPlan<LOGN>::NP + 1, a.tw[LOGN],
+  fold_class<LOGN, M, PREC, kDescBlock>(im, r, tid, lds, lds + (M / 2) * FftPlan<LOGN>::NP + 1, a.tw[LOGN],
                                         a.tw[LOGN] + tw_size(LOGN), SplitCtx{s_max, a.dft_ops});
 }
 
@@ -92,6 +91,13 @@ __global__ __launch_bounds__(kDescBlock, 4) void k_fold_desc(DescArgs a, unsigne
   for (unsigned item = first_item + blockIdx.x;; item += gridDim.x) {
     // the size, and the item within it (uniform over the workgroup)
     unsigned w = item;
+    int tid = threadIdx.x;
+    if (LOOP) {
+      // what follows from the thread's index is formed again for every item: kept over the loop it took
+      // 1120 (FP32) to 1608 bytes of scratch memory a lane, outside the caller's workspace
+      asm volatile("" : "+v"(tid));
+      __builtin_assume(tid >= 0 && tid < kDescBlock);
+    }
     int l = a.max_logn, lo = 0, count = 0;
     for (; l >= 3; --l) {
       const int4 z = a.sizes[l];
@@ -103,16 +109,16 @@ __global__ __launch_bounds__(kDescBlock, 4) void k_fold_desc(DescArgs a, unsigne
       w -= n;
     }
     switch (l) {
-      case 3: fold_desc_item<3, PREC>(a, lo, count, w, lds, &s_max); break;
-      case 4: fold_desc_item<4, PREC>(a, lo, count, w, lds, &s_max); break;
-      case 5: fold_desc_item<5, PREC>(a, lo, count, w, lds, &s_max); break;
-      case 6: fold_desc_item<6, PREC>(a, lo, count, w, lds, &s_max); break;
-      case 7: fold_desc_item<7, PREC>(a, lo, count, w, lds, &s_max); break;
-      case 8: fold_desc_item<8, PREC>(a, lo, count, w, lds, &s_max); break;
-      case 9: fold_desc_item<9, PREC>(a, lo, count, w, lds, &s_max); break;
-      case 10: fold_desc_item<10, PREC>(a, lo, count, w, lds, &s_max); break;
-      case 11: fold_desc_item<11, PREC>(a, lo, count, w, lds, &s_max); break;
-      case 12: fold_desc_item<12, PREC>(a, lo, count, w, lds, &s_max); break;
+      case 3: fold_desc_item<3, PREC>(a, lo, count, w, tid, lds, &s_max); break;
+      case 4: fold_desc_item<4, PREC>(a, lo, count, w, tid, lds, &s_max); break;
+      case 5: fold_desc_item<5, PREC>(a, lo, count, w, tid, lds, &s_max); break;
+      case 6: fold_desc_item<6, PREC>(a, lo, count, w, tid, lds, &s_max); break;
+      case 7: fold_desc_item<7, PREC>(a, lo, count, w, tid, lds, &s_max); break;
+      case 8: fold_desc_item<8, PREC>(a, lo, count, w, tid, lds, &s_max); break;
+      case 9: fold_desc_item<9, PREC>(a, lo, count, w, tid, lds, &s_max); break;
+      case 10: fold_desc_item<10, PREC>(a, lo, count, w, tid, lds, &s_max); break;
+      case 11: fold_desc_item<11, PREC>(a, lo, count, w, tid, lds, &s_max); break;
+      case 12: fold_desc_item<12, PREC>(a, lo, count, w, tid, lds, &s_max); break;
       default: return;                             // past the last item
     }
     if (!LOOP) return;

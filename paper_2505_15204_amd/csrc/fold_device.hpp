@@ -99,7 +99,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t fold_rsrc(const void* p, int b
 // transform buffer, and one word behind them for the padding placements. The workgroup has BLOCK >=
 // M N / 32 threads; the others only join the barriers and the loops over columns.
 template <int LOGN, int M, int PREC, int BLOCK>
-__device__ __forceinline__ void fold_class(const FoldImage& im, int r, float2* sbuf, float2* s_w,
+__device__ __forceinline__ void fold_class(const FoldImage& im, int r, int tid, float2* sbuf, float2* s_w,
                                            const float2* __restrict__ tw, const float2* __restrict__ lin, SplitCtx sp) {
   using P = FftPlan<LOGN>;
   using FR = FoldRadix<M>;
@@ -107,7 +107,7 @@ __device__ __forceinline__ void fold_class(const FoldImage& im, int r, float2* s
   constexpr int A = FR::A, B = FR::B;
   constexpr bool SPLIT = PREC != kPrecFp32 && LOGN >= 4;
   static_assert(BLOCK % 64 == 0 && BLOCK >= NT, "whole waves");
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int ext = im.hdr->ext, first_over = im.hdr->first_over, n_over = im.hdr->n_over, n_ent = first_over + n_over;
   const bool folds = BLOCK / 64 == NW || wave < NW;   // uniform over the wave
@@ -325,7 +325,7 @@ __device__ __forceinline__ void fold_class(const FoldImage& im, int r, float2* s
                                                [&](int c, int e, float2 z) {
                                                  __builtin_nontemporal_store(z.x, row_at(2 * c) + e);
                                                  __builtin_nontemporal_store(z.y, row_at(2 * c + 1) + e);
-                                               }, sp);
+                                               }, sp, tid);
   } else {
     float* o1 = row_at(2 * j);
     float* o2 = row_at(2 * j + 1);

@@ -212,10 +212,10 @@ __device__ __forceinline__ int split_out_j(int g, int t) { return 4 * (t >> 1) +
 
 // Largest |re| or |im| over the block. *s_max must be 0 and visible to every thread on entry
 // (set before an earlier barrier); it keeps the maximum afterwards. Contains a block barrier.
-__device__ __forceinline__ float block_max_abs(float m, unsigned* s_max) {
+__device__ __forceinline__ float block_max_abs(float m, unsigned* s_max, int tid) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-  if ((threadIdx.x & 63) == 0) atomicMax(s_max, __float_as_uint(m));
+  if ((tid & 63) == 0) atomicMax(s_max, __float_as_uint(m));
   __syncthreads();
   return __uint_as_float(*s_max);
 }
@@ -261,13 +261,13 @@ __device__ __forceinline__ int f16_scale_exponent(float mx) {
 // waves and use workgroup barriers.
 template <int LOGN, int PREC, bool ToLds, bool FromBuf, class Load, class Sink>
 __device__ __forceinline__ void fft_inverse_split(float2* buf, int ntrans, const float2* __restrict__ tw, Load load,
-                                                  Sink sink, SplitCtx sp) {
+                                                  Sink sink, SplitCtx sp, int tid = threadIdx.x) {
   using P = FftPlan<LOGN>;
   static_assert(LOGN >= 4, "the split form needs at least one radix-16 stage");
   static_assert(PREC == kPrecSplitF16 || PREC == kPrecSplitBf16, "split precision");
   constexpr int N = P::N, T = P::T, NP = P::NP, NB = N / 16;
   const DftOperands<PREC> F = dft16_operands<PREC>(sp.ops);
-  const int lane = threadIdx.x & 63, n = lane & 31, g = lane >> 5, w = threadIdx.x >> 6;
+  const int lane = tid & 63, n = lane & 31, g = lane >> 5, w = tid >> 6;
   const int total = ntrans * NB;
   constexpr bool WAVE_LOCAL = NB <= 64;   // T == NB: stage_sync<T> orders within the wave
 
@@ -343,7 +343,7 @@ __device__ __forceinline__ void fft_inverse_split(float2* buf, int ntrans, const
       e = f16_scale_exponent(wave_max_abs(m));
       stage_sync<T>();                   // every load of buf is done before the in-place stores
     } else {
-      e = f16_scale_exponent(block_max_abs(m, sp.s_max));   // also: every load of buf is done
+      e = f16_scale_exponent(block_max_abs(m, sp.s_max, tid));   // also: every load of buf is done
     }
     const float s = ldexpf(1.f, e);
     u = ldexpf(1.f, -e);
@@ -391,7 +391,7 @@ __device__ __forceinline__ void fft_inverse_split(float2* buf, int ntrans, const
     auto valu_stage = [&](auto ns_tag, auto rad_tag) {
       // final small-radix stage in FP32, one thread per group of 16 elements as in fft_inverse
       constexpr int NS = decltype(ns_tag)::value, RAD = decltype(rad_tag)::value;
-      const int c = threadIdx.x / T, lt = threadIdx.x % T;
+      const int c = tid / T, lt = tid % T;
       const bool active = c < ntrans;
       float2 v[16];
       if (active) {
