@@ -665,15 +665,20 @@ static blink_status image_batch(blink_ctx ctx, const blink_cf32* vis, const uint
     return blink::launch_correct_vis(xa, s);
   };
   // The folded path takes the sizes and baseline counts that its layout holds from 512^2 on: it is
-  // faster than the two-pass form below at all of them (64 images of 1024^2: 121 against 225 us per call;
-  // 1536: 2.34 against 4.10 ms; 16 of 4096^2 in the split FP16 form: 0.50 against 1.30 ms; 130 of 512^2
-  // with corrections: 87 against 163 us; one of 512^2 with 276 baselines: 29.5 against 30.3 us). At 256^2
-  // its binning takes longer than it saves for few images of few baselines (630 baselines: 1 image 29
-  // against 21 us, 18 images 30 against 24, 300 images 65 against 70; 8128 baselines: 1 image 43
-  // against 49), and up to 128^2 it always does (600 images, 8128 baselines: 120 against 108 us; 300,
-  // 10296 baselines: 105 against 84). The two-pass form serves those, larger arrays and workspaces
-  // that do not hold one pair's placement lists.
-  const bool folds = logn > 8 || (logn == 8 && (B >= 4096 || n_tc * P >= 192));
+  // faster than the two-pass form below at all of them (64 images of 1024^2: 116 against 225 us per call;
+  // 1536: 2.27 against 4.10 ms; 16 of 4096^2 in the split FP16 form: 0.50 against 1.30 ms; 130 of 512^2
+  // with corrections: 81 against 163 us; one of 512^2 with 276 baselines: 27 against 31 us) except where all
+  // placements lie within a few cells of the centre of a much larger grid, which the host cannot know: the
+  // two-pass form leaves out the empty columns (8128 within 20 cells, 256 images of 1024^2: 386 against
+  // 356 us; 8 of 4096^2: 246 against 184). At 256^2 its binning takes longer than it saves for few images
+  // of few baselines (630 baselines: 18 images 30 against 24 us, 300 images 65 against 70), and with 4096 and more
+  // baselines for few images where the two-pass form is at its best: uniform weighting (8128 baselines: 1 image
+  // 46 against 33 us, 96 images 53 against 52, 128 images 56 against 68) and the split FP16 form (natural: 1 image
+  // 37 against 34, 64 images 39 against 43); natural FP32 and BF16 gain from one image on (36 against 39, 37
+  // against 44). Up to 128^2 it always loses (600 images, 8128 baselines: 120 against 108 us; 300, 10296
+  // baselines: 105 against 84). The two-pass form serves those and larger arrays.
+  const size_t n_img256 = B < 4096 ? 192 : weighting ? 128 : precision == BLINK_PREC_SPLIT_F16 ? 64 : 1;
+  const bool folds = logn > 8 || (logn == 8 && n_tc * P >= n_img256);
   if (folds && B > 0 && B <= blink::kFoldMaxB) {
     const int m = blink::fold_rows(logn);
     const size_t Q = largest_fitting_chunk(n_tc, workspace_bytes,

@@ -1,0 +1,56 @@
+"""Which form a call takes, by the launches that the context's kernel timing counts: the two-pass form
+launches row kernels, the folded form none.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+FREQ = 150.0e6
+DL = 1.0e-3
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as _t
+    if not _t.cuda.is_available():
+        pytest.skip("no GPU")
+    return _t
+
+
+@pytest.fixture(scope="module")
+def ctx(torch):
+    import paper_2505_15204_amd as blink
+    c = blink.Context(0)
+    yield c
+    c.close()
+
+
+def row_launches(torch, ctx, call):
+    ctx.profile_enable(True)
+    call()
+    torch.cuda.synchronize()
+    launches = ctx.profile_read()["row_fft"][1]
+    ctx.profile_enable(False)
+    return launches
+
+
+def image_call(torch, ctx, B, N, C, weighting, prec):
+    g = np.random.default_rng(B + N)
+    d = "cuda:0"
+    uvw = np.zeros((1, B, 3))
+    uvw[0, :, :2] = g.uniform(-N / 2 + 1, N / 2 - 1, (B, 2)) / (FREQ / 299792458.0 * (N * DL))
+    vis = torch.randn((1, C, 1, B), device=d, dtype=torch.complex64)
+    uvw, freq = torch.from_numpy(uvw).to(d), torch.full((C,), FREQ, dtype=torch.float64, device=d)
+    return lambda: ctx.blink_image_batch(vis, None, uvw, freq, N, DL, weighting, precision=prec)
+
+
+# both sides of the lines at 256^2, and the sizes beside it
+@pytest.mark.parametrize("B,N,C,weighting,prec,folded", [
+    (4095, 256, 191, 0, 0, False), (300, 256, 192, 0, 0, True), (4096, 256, 1, 0, 0, True), (4096, 256, 1, 0, 2, True),
+    (4096, 256, 63, 0, 1, False), (4096, 256, 64, 0, 1, True), (4096, 256, 1, 1, 0, False), (8128, 256, 127, 1, 0, False),
+    (8128, 256, 128, 1, 0, True), (8128, 256, 127, 1, 1, False), (300, 256, 192, 1, 2, True), (45, 512, 1, 1, 1, True),
+    (8128, 128, 300, 0, 0, False), (16384, 512, 1, 0, 0, True), (16385, 512, 1, 0, 0, False)])
+def test_image_batch(torch, ctx, B, N, C, weighting, prec, folded):
+    print(f"[gpu-case] route B={B} N={N} C={C} w={weighting} prec={prec}", flush=True)
+    assert (row_launches(torch, ctx, image_call(torch, ctx, B, N, C, weighting, prec)) == 0) == folded
