@@ -1372,7 +1372,13 @@ blink_status run_desc_folded(blink_ctx ctx, const DescCall& c, int max_logn, siz
 // down and every chunk slot reserved for it, the chunk's column launch and row launch with the
 // batched path's plan for that size (strip width, strips per workgroup, row block).
 blink_status run_desc_staged(blink_ctx ctx, const DescCall& c, int max_logn, hipStream_t s) {
-  if (c.max_b <= blink::kFoldMaxB && staged_layout(c.n_img, c.max_b, c.max_n).total <= c.ws_bytes) {
+  // Batches of small grids only: an image is one item of 512 threads (32^2: 32 of them at work in the
+  // transforms), which pays where the binning's sort is what costs: 400 images of 32^2, 1500 baselines: 102 us
+  // against 61 in chunks, 4500: 95 against 132; 16^2, 45 baselines, 2000 images: 307 against 56, 3000 baselines:
+  // 184 against 343; 64^2, 4500 baselines, 400 images: 97 against 93, 2000 images: 261 against 320. From
+  // 128^2 on it is faster at all (20 images, 45 baselines: 39 against 46).
+  const bool folds = c.max_n >= 128 || (c.max_b >= (c.max_n <= 16 ? 2048 : 4096) && (c.max_n < 64 || c.n_img >= 1024));
+  if (folds && c.max_b <= blink::kFoldMaxB && staged_layout(c.n_img, c.max_b, c.max_n).total <= c.ws_bytes) {
     // Folded wherever the binning keeps an image's baselines in registers (400 images, 2721 -> 1500 us),
     // at least 64 images at a time (or the batch): fewer would leave the binning launches idle.
     const size_t n_pos = largest_fitting_chunk((size_t)c.n_img, c.ws_bytes, [&](size_t n) {

@@ -54,3 +54,29 @@ def image_call(torch, ctx, B, N, C, weighting, prec):
 def test_image_batch(torch, ctx, B, N, C, weighting, prec, folded):
     print(f"[gpu-case] route B={B} N={N} C={C} w={weighting} prec={prec}", flush=True)
     assert (row_launches(torch, ctx, image_call(torch, ctx, B, N, C, weighting, prec)) == 0) == folded
+
+
+def desc_call(torch, ctx, N, B, n_img):
+    import paper_2505_15204_amd as blink
+
+    g = np.random.default_rng(B + N)
+    d = "cuda:0"
+    desc = np.zeros(n_img, blink.DESC_DTYPE)
+    desc["grid_n"], desc["n_baselines"], desc["freq_hz"], desc["pixel_scale"] = N, B, FREQ, DL
+    desc["image_offset"] = np.arange(n_img) * N * N
+    uvw = np.zeros((B, 3))                           # every image reads the same visibilities
+    uvw[:, :2] = g.uniform(-N / 2 + 1, N / 2 - 1, (B, 2)) / (FREQ / 299792458.0 * (N * DL))
+    vis = torch.randn((B,), device=d, dtype=torch.complex64)
+    out = torch.empty(n_img * N * N, device=d)
+    ws = torch.empty(blink.desc_workspace_size(n_img, B, N) + (1 << 26), dtype=torch.uint8, device=d)
+    desc, uvw = torch.from_numpy(desc.view(np.uint8).copy()).to(d), torch.from_numpy(uvw).to(d)
+    return lambda: ctx.blink_image_batch_desc(desc, vis, uvw, None, out, B, N, workspace=ws)
+
+
+@pytest.mark.parametrize("N,B,n_img,folded", [(128, 45, 20, True), (64, 8000, 400, False), (64, 4096, 1024, True),
+                                              (64, 45, 1024, False), (32, 4095, 400, False), (32, 4096, 100, True),
+                                              (16, 45, 400, False), (16, 2048, 100, True), (8, 45, 2000, False)])
+def test_uneven_batch(torch, ctx, N, B, n_img, folded):
+    print(f"[gpu-case] route uneven N={N} B={B} n_img={n_img}", flush=True)
+    ctx.set_desc_plan(512, 0, form=1)
+    assert (row_launches(torch, ctx, desc_call(torch, ctx, N, B, n_img)) == 0) == folded
