@@ -329,12 +329,16 @@ hipError_t launch_image_average(const float* in, int T, int C, int P, int logn, 
   if ((nn4 + 63) / 64 * n_img > 0x7fffffffL) return hipErrorInvalidValue;
   // Below 16 inputs the sum is short, and it is below 64 where the pixels alone fill the chip: there
   // plain loads with a thread per pixel quad (40 inputs of 2048^2: 119 us, 126 with 8 slices; 3 inputs: 11.6
-  // and 13.4) unless there are many outputs (80 of 2 inputs of 1024^2: 155 us against 167 plain). 84
-  // inputs of 2048^2 take 235 us with 8 slices, 250 plain. Below 2048 blocks of 256 pixels (256^2 and smaller, one output)
-  // more waves per output are needed than the 8 slices of the wider form give: 8400 images of
-  // 256^2 take 337 us with 16 slices, 3886 us with one; 1536 of 1024^2 1055 us with 8 slices of 512
-  // pixels, 1078 with 4 of 256, 1228 with 4 of 1024, 1211 with one (one thread per pixel quad).
-  if (n < 16 ? n_img == 1 : n < 64 && blocks(1) >= 2048)
+  // and 13.4), unless there are many outputs and more data than the last-level cache keeps, which the 64-thread
+  // blocks' loads pass by (80 of 2 inputs of 1024^2: 155 us against 167 plain; but 80 of 2 of 256^2, 63
+  // MB: 14.9 against 11.9) and which need whole waves of an image's pixels (80000 of 2 inputs of 8^2: 37.3
+  // against 11.7). 84 inputs of 2048^2 take 235 us with 8 slices, 250 plain. Below 2048 blocks of 256 pixels
+  // (256^2 and smaller, one output; from 512 on short sums stay plain: 100 outputs of 20 inputs of 64^2 15.8
+  // us with 16 slices, 8.7 plain) more waves per output are needed than the 8 slices of the wider form give:
+  // 8400 images of 256^2 take 337 us with 16 slices, 3886 us with one; 1536 of 1024^2 1055 us with 8 slices of
+  // 512 pixels, 1078 with 4 of 256, 1228 with 4 of 1024, 1211 with one (one thread per pixel quad).
+  const bool streams = (n + 1) * n_img * nn4 * 16 > 300000000L && nn4 >= 256;
+  if (n < 16 ? n_img == 1 || !streams : n < 64 && blocks(1) >= (n < 32 ? 512u : 2048u))
     k_image_average_few<<<blocks(4), 256, 0, s>>>(src, C, P, nn4, axes, Co, Po, nn4 * n_img, r, dst);
   else if (n < 16) k_image_average<1, 1><<<blocks(1), 64, 0, s>>>(src, C, P, nn4, axes, Co, Po, r, dst);
   else if (blocks(1) >= 2048) k_image_average<8, 2><<<blocks(2), 1024, 0, s>>>(src, C, P, nn4, axes, Co, Po, r, dst);
