@@ -284,23 +284,27 @@ __global__ __launch_bounds__(64 * SLICES * WIDTH) void k_image_average(const f32
   if (px < nn4) out[img * nn4 + px] = f32x4{(float)(a[0] * inv), (float)(a[1] * inv), (float)(a[2] * inv), (float)(a[3] * inv)};
 }
 
-// One thread per pixel quad and output, every input through the caches: for one output of few inputs.
-__global__ __launch_bounds__(256) void k_image_average_few(const f32x4* __restrict__ in, int C, int P, long nn4,
-                                                           int axes, int Co, int Po, long n_quads, AvgRuns r,
+// One thread per pixel quad and output, every input through the caches: for short sums. Small images leave a
+// thread little but its index to work out, which takes 32-bit divisions (80000 outputs of two inputs of
+// 8^2: 26.7 us with 64-bit ones and a product per input).
+__global__ __launch_bounds__(256) void k_image_average_few(const f32x4* __restrict__ in, int C, int P, int log_nn4,
+                                                           int axes, unsigned Co, unsigned Po, long n_quads, AvgRuns r,
                                                            f32x4* __restrict__ out) {
   const long gid = (long)blockIdx.x * 256 + threadIdx.x;
   if (gid >= n_quads) return;
-  const long img = gid / nn4, px = gid - img * nn4;
-  const int po = (int)(img % Po), co = (int)((img / Po) % Co), to = (int)(img / ((long)Po * Co));
-  const long first = ((long)((axes & 1) ? 0 : to) * C + ((axes & 2) ? 0 : co)) * P + ((axes & 4) ? 0 : po);
-  const f32x4* src = in + first * nn4 + px;
+  const unsigned img = (unsigned)(gid >> log_nn4), tc = img / Po, po = img - tc * Po, to = tc / Co, co = tc - to * Co;
+  const long first = ((long)((axes & 1) ? 0u : to) * C + ((axes & 2) ? 0u : co)) * P + ((axes & 4) ? 0u : po);
+  const f32x4* src = in + (first << log_nn4) + (gid & ((1L << log_nn4) - 1));
+  const long step1 = r.s1 << log_nn4, step2 = r.s2 << log_nn4;
   double a[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int i = 0; i < r.n2; ++i)
-    for (int j = 0; j < r.n1; ++j) {
-      const f32x4 v = src[(i * r.s2 + j * r.s1) * nn4];
+  for (int i = 0; i < r.n2; ++i, src += step2) {
+    const f32x4* p = src;
+    for (int j = 0; j < r.n1; ++j, p += step1) {
+      const f32x4 v = *p;
 #pragma unroll
       for (int q = 0; q < 4; ++q) a[q] += (double)v[q];
     }
+  }
   const double inv = 1.0 / ((double)r.n1 * r.n2);
   out[gid] = f32x4{(float)(a[0] * inv), (float)(a[1] * inv), (float)(a[2] * inv), (float)(a[3] * inv)};
 }
@@ -339,7 +343,8 @@ hipError_t launch_image_average(const float* in, int T, int C, int P, int logn, 
   // 512 pixels, 1078 with 4 of 256, 1228 with 4 of 1024, 1211 with one (one thread per pixel quad).
   const bool streams = (n + 1) * n_img * nn4 * 16 > 300000000L && nn4 >= 256;
   if (n < 16 ? n_img == 1 || !streams : n < 64 && blocks(1) >= (n < 32 ? 512u : 2048u))
-    k_image_average_few<<<blocks(4), 256, 0, s>>>(src, C, P, nn4, axes, Co, Po, nn4 * n_img, r, dst);
+    k_image_average_few<<<(unsigned)((nn4 * n_img + 255) / 256), 256, 0, s>>>(src, C, P, 2 * logn - 2, axes, Co, Po,
+                                                                                nn4 * n_img, r, dst);
   else if (n < 16) k_image_average<1, 1><<<blocks(1), 64, 0, s>>>(src, C, P, nn4, axes, Co, Po, r, dst);
   else if (blocks(1) >= 2048) k_image_average<8, 2><<<blocks(2), 1024, 0, s>>>(src, C, P, nn4, axes, Co, Po, r, dst);
   else k_image_average<16, 1><<<blocks(1), 1024, 0, s>>>(src, C, P, nn4, axes, Co, Po, r, dst);
