@@ -109,7 +109,10 @@ blink_status blink_grid_workspace_size(int T, int C, int B, int grid_n, size_t *
 /* Workspace bytes for blink_ifft2d over n_img grids of side grid_n. */
 blink_status blink_ifft2d_workspace_size(int n_img, int grid_n, int precision, size_t *bytes);
 
-/* Workspace bytes for blink_image_batch to process all T*C (time, channel) pairs in one chunk. */
+/* Workspace bytes for blink_image_batch to process all T*C (time, channel) pairs in one chunk of the
+ * two-pass form. The folded form's lists take 12 bytes a placement in place of 8, but no intermediate: where
+ * they outgrow these bytes (many baselines on a small grid) it takes the pairs in a few chunks. Smaller
+ * workspaces are accepted down to the two-pass form's bytes for one pair and one intermediate, in either form. */
 blink_status blink_image_batch_workspace_size(int T, int C, int P, int B, int grid_n,
                                               int weighting, int precision, size_t *bytes);
 

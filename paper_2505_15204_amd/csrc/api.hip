@@ -677,6 +677,11 @@ static blink_status image_batch(blink_ctx ctx, const blink_cf32* vis, const uint
   // 37 against 34, 64 images 39 against 43); natural FP32 and BF16 gain from one image on (36 against 39, 37
   // against 44). Up to 128^2 it always loses (600 images, 8128 baselines: 120 against 108 us; 300, 10296
   // baselines: 105 against 84). The two-pass form serves those and larger arrays.
+  // A workspace has to hold one pair of the two-pass form, whichever form the call takes: callers meet one limit.
+  const ImageLayout one = image_layout(1, P, B, logn, weighting, 1, corrected);
+  if (!one.ok || one.total > workspace_bytes)
+    return fail(ctx, BLINK_ERR_SIZE, "workspace of %zu bytes is smaller than one (t,c) pair needs (%zu)", workspace_bytes,
+                one.total);
   const size_t n_img256 = B < 4096 ? 192 : weighting ? 128 : precision == BLINK_PREC_SPLIT_F16 ? 64 : 1;
   const bool folds = logn > 8 || (logn == 8 && n_tc * P >= n_img256);
   if (folds && B > 0 && B <= blink::kFoldMaxB) {
@@ -755,13 +760,10 @@ static blink_status image_batch(blink_ctx ctx, const blink_cf32* vis, const uint
     return image_layout(q, P, B, logn, weighting, q * P < want ? q * P : want, corrected).total;
   });
   size_t h_images = Q * P < want ? Q * P : want;
-  if (Q == 0 && image_layout(1, P, B, logn, weighting, 1, corrected).total <= workspace_bytes) {
-    Q = 1;                       // fall back to one intermediate at a time
+  if (Q == 0) {                  // one intermediate at a time (the layout checked above)
+    Q = 1;
     h_images = 1;
   }
-  if (Q == 0)
-    return fail(ctx, BLINK_ERR_SIZE, "workspace of %zu bytes is smaller than one (t,c) pair needs (%zu)",
-                workspace_bytes, image_layout(1, P, B, logn, weighting, 1, corrected).total);
   if (Q * P > (size_t)INT32_MAX) return fail(ctx, BLINK_ERR_SIZE, "batch too large");
   DeviceGuard g(ctx->device);
   if (g.err != hipSuccess) return hip_fail(ctx, g.err, "hipSetDevice");
