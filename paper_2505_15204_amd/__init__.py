@@ -363,7 +363,8 @@ class Context:
     @_on_stream
     def autotune_image_batch(self, vis, flags, uvw_m, freq_hz, grid_n: int, pixel_scale: float, weighting: int = 0,
                              precision: int = PREC_FP32, shift: bool = True, out=None, workspace=None, stream=None):
-        """Time every compiled plan on this problem and keep the fastest; returns (plan dict, best ms)."""
+        """Time every compiled plan of the two-pass form (which blink_ifft2d, blink_image_batch_conv and the batches
+        that are not folded use) on this problem and keep the fastest; returns (plan dict, best ms)."""
         torch = self._torch()
         T, C, P, B = vis.shape
         N = int(grid_n)

@@ -631,11 +631,12 @@ static FoldLayout fold_layout(size_t Q, int P, int B, bool corrected) {
 }
 
 // blink_image_batch, and blink_image_batch_corrected when corr is non-null (checked by the caller).
+// two_pass: never the folded form (the autotuner times the form that plans steer).
 static blink_status image_batch(blink_ctx ctx, const blink_cf32* vis, const uint8_t* flags, const double* uvw_m,
                                 const double* freq_hz, int T, int C, int P, int B, int grid_n, double pixel_scale,
                                 int weighting, int precision, int shift, const blink_corrections* corr,
                                 float* images, double* weight_sum, int32_t* n_out, void* workspace,
-                                size_t workspace_bytes, void* hip_stream) {
+                                size_t workspace_bytes, void* hip_stream, bool two_pass = false) {
   int logn = 0;
   blink_status st = check_problem(ctx, vis, uvw_m, freq_hz, T, C, P, B, grid_n, pixel_scale, weighting,
                                   images, workspace, &logn);
@@ -683,7 +684,7 @@ static blink_status image_batch(blink_ctx ctx, const blink_cf32* vis, const uint
     return fail(ctx, BLINK_ERR_SIZE, "workspace of %zu bytes is smaller than one (t,c) pair needs (%zu)", workspace_bytes,
                 one.total);
   const size_t n_img256 = B < 4096 ? 192 : weighting ? 128 : precision == BLINK_PREC_SPLIT_F16 ? 64 : 1;
-  const bool folds = logn > 8 || (logn == 8 && n_tc * P >= n_img256);
+  const bool folds = !two_pass && (logn > 8 || (logn == 8 && n_tc * P >= n_img256));
   if (folds && B > 0 && B <= blink::kFoldMaxB) {
     const int m = blink::fold_rows(logn);
     const size_t Q = largest_fitting_chunk(n_tc, workspace_bytes,
@@ -1775,8 +1776,8 @@ blink_status blink_autotune_image_batch(blink_ctx ctx, const blink_cf32* vis, co
     double t = 1e300;
     for (int rep = 0; rep < 3 && result == BLINK_OK; ++rep) {
       hipError_t he = hipEventRecord(e0, s);
-      result = blink_image_batch(ctx, vis, flags, uvw_m, freq_hz, T, C, P, B, grid_n, pixel_scale, weighting,
-                                 precision, shift, images, weight_sum, n_out, workspace, workspace_bytes, hip_stream);
+      result = image_batch(ctx, vis, flags, uvw_m, freq_hz, T, C, P, B, grid_n, pixel_scale, weighting, precision, shift,
+                           nullptr, images, weight_sum, n_out, workspace, workspace_bytes, hip_stream, true);
       if (he == hipSuccess) he = hipEventRecord(e1, s);
       if (he == hipSuccess) he = hipEventSynchronize(e1);
       float ms = 0.f;
@@ -1821,8 +1822,8 @@ blink_status blink_autotune_image_batch(blink_ctx ctx, const blink_cf32* vis, co
   ctx->plan[logn][weighting][precision] = result == BLINK_OK ? best_plan : saved;
   if (result != BLINK_OK) return result;
   // leave a result computed with the chosen plan in the outputs
-  result = blink_image_batch(ctx, vis, flags, uvw_m, freq_hz, T, C, P, B, grid_n, pixel_scale, weighting, precision,
-                             shift, images, weight_sum, n_out, workspace, workspace_bytes, hip_stream);
+  result = image_batch(ctx, vis, flags, uvw_m, freq_hz, T, C, P, B, grid_n, pixel_scale, weighting, precision, shift,
+                       nullptr, images, weight_sum, n_out, workspace, workspace_bytes, hip_stream, true);
   if (col_strip) *col_strip = best_plan.col_strip;
   if (row_block) *row_block = best_plan.row_tpb;
   if (group) *group = best_plan.group;

@@ -1,4 +1,7 @@
-"""Autotune the execution plans of blink_image_batch on this GPU and write them to a plan file.
+"""Autotune the execution plans of the two-pass imaging form on this GPU and write them to a plan file.
+
+Plans steer blink_ifft2d, blink_image_batch_conv and those calls of blink_image_batch and its variants that are not
+folded (small grids, more than 16384 baselines); the tuner times that form at every size.
 
 For every grid size, weighting and precision form asked for, one time step of a synthetic
 MWA-shaped workload of that size is imaged with every compiled (strip width, row block) pair and
