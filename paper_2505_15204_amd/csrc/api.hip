@@ -517,7 +517,7 @@ blink_status blink_grid(blink_ctx ctx, const blink_cf32* vis, const uint8_t* fla
     ba.logn = logn;
     ba.log_strip = log_s;
     ba.ku_limit = (int)N;
-    ba.rows = 1;
+    ba.tiles = 1;
     ba.P = P;
     ba.pixel_scale = pixel_scale;
     ba.plc = (int2*)(ws + L.bins.plc);

@@ -14,6 +14,7 @@ constexpr int kLdsBytes = 160 * 1024;
 constexpr double kSpeedOfLight = 299792458.0;
 constexpr int kBinThreads = 1024;
 constexpr int kMaxStrips = 4096;
+constexpr int kLogTileRows = 6;              // rows of a tile of the full grid (blink_grid)
 // Fourth word of a raw buffer resource on gfx9-family chips (gfx950): 32-bit data format, no
 // swizzle, no index stride; with it a load at or past the resource's byte size returns zero.
 constexpr int kBufferRsrcWord3 = 0x00020000;
@@ -88,10 +89,10 @@ struct BinShared {
 // record {kv*N + ku, b | conj<<31}), the strip offsets off[0..ku_limit>>log_strip], the kept and
 // out-of-grid counts, and cell_idx[b] when non-null. When ext_out is non-null it receives the
 // column extent: (index of the last strip holding a placement + 1) * 2^log_strip, 0 when no
-// placement is kept; every column at or beyond it is zero in the grid. With ROWS the strips are
-// 2^log_strip rows instead (kv in place of ku; the whole grid, ku_limit = N). One workgroup (a
-// multiple of 64 threads, at least 512 so that the strip count fits the scan).
-template <bool ROWS = false>
+// placement is kept; every column at or beyond it is zero in the grid. With TILES the strips are tiles
+// of as many cells instead, of up to 64 rows, in row order (the whole grid, ku_limit = N). One
+// workgroup (a multiple of 64 threads, at least 512 so that the strip count fits the scan).
+template <bool TILES = false>
 __device__ inline void bin_visibilities(const double* __restrict__ uvw, const uint8_t* __restrict__ fl, int B,
                                         double k, int logn, int log_strip, int ku_limit, int2* __restrict__ plc,
                                         int* __restrict__ off, int* kept_out, int* nout_out,
@@ -99,6 +100,10 @@ __device__ inline void bin_visibilities(const double* __restrict__ uvw, const ui
   const int N = 1 << logn, mask = N - 1;
   const int nstrips = ku_limit >> log_strip;
   const double half = (double)(N / 2);
+  const int log_h = logn < kLogTileRows ? logn : kLogTileRows, log_w = logn + log_strip - log_h;   // of a tile
+  auto strip_of = [&](int ku, int kv) {
+    return TILES ? (kv >> log_h) << (logn - log_w) | ku >> log_w : ku >> log_strip;
+  };
   for (int i = threadIdx.x; i <= nstrips; i += blockDim.x) sh.cnt[i] = 0;
   if (threadIdx.x < 3) sh.red[threadIdx.x] = 0;
   __syncthreads();
@@ -108,12 +113,11 @@ __device__ inline void bin_visibilities(const double* __restrict__ uvw, const ui
     if (!(fl && fl[b])) {
       int iu, iv;
       if (nearest_cell(uvw[3 * b], uvw[3 * b + 1], k, half, iu, iv)) {
-        const int ku1 = iu & mask, kv1 = iv & mask, ku2 = (-iu) & mask;
+        const int ku1 = iu & mask, kv1 = iv & mask, ku2 = (-iu) & mask, kv2 = (-iv) & mask;
         cell = kv1 * N + ku1;
         ++kept;
-        const int s1 = ROWS ? kv1 : ku1, s2 = ROWS ? (-iv) & mask : ku2;
-        if (ku1 < ku_limit) atomicAdd(&sh.cnt[s1 >> log_strip], 1);
-        if (ku2 < ku_limit) atomicAdd(&sh.cnt[s2 >> log_strip], 1);
+        if (ku1 < ku_limit) atomicAdd(&sh.cnt[strip_of(ku1, kv1)], 1);
+        if (ku2 < ku_limit) atomicAdd(&sh.cnt[strip_of(ku2, kv2)], 1);
       } else {
         cell = -2;
         ++outside;
@@ -143,11 +147,11 @@ __device__ inline void bin_visibilities(const double* __restrict__ uvw, const ui
     const int ku1 = iu & mask, kv1 = iv & mask;
     const int ku2 = (-iu) & mask, kv2 = (-iv) & mask;
     if (ku1 < ku_limit) {
-      int pos = atomicAdd(&sh.cnt[(ROWS ? kv1 : ku1) >> log_strip], 1);
+      int pos = atomicAdd(&sh.cnt[strip_of(ku1, kv1)], 1);
       plc[pos] = make_int2(kv1 * N + ku1, b);
     }
     if (ku2 < ku_limit) {
-      int pos = atomicAdd(&sh.cnt[(ROWS ? kv2 : ku2) >> log_strip], 1);
+      int pos = atomicAdd(&sh.cnt[strip_of(ku2, kv2)], 1);
       plc[pos] = make_int2(kv2 * N + ku2, (int)((unsigned)b | 0x80000000u));
     }
   }

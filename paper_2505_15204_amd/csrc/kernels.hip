@@ -4,7 +4,7 @@
 //   k_bin            cell indices (FP64 product + rint), flags, out-of-grid drop, counting sort
 //                    of the placements into column strips (Section 6.2.4 gridding, one
 //                    workgroup per (time, channel), shared by the polarisations)
-//   k_grid_full      LDS-private strips of rows -> complex grid in HBM, counts
+//   k_grid_full      LDS-private tiles -> complex grid in HBM, counts
 //   k_grid_colfft    LDS-private strip grid -> inverse FFT along v -> half-spectrum H
 //   k_dense_colfft   Hermitian part of a dense grid -> inverse FFT along v -> H
 //   k_row_c2r        two H rows -> Hermitian-extended inverse FFT along u -> two image rows,
@@ -77,7 +77,7 @@ hipError_t launch_twiddles(float2* tw, int logn, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------- binning
-template <bool ROWS>
+template <bool TILES>
 __global__ __launch_bounds__(kBinThreads) void k_bin(BinArgs a) {
   __shared__ BinShared sh;
   const int tcl = blockIdx.x;
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bin(BinArgs a) {
   const int N = 1 << a.logn;
   const int nstrips = a.ku_limit >> a.log_strip;
   const double k = (a.freq[c] / kSpeedOfLight) * ((double)N * a.pixel_scale);
-  bin_visibilities<ROWS>(a.uvw + (size_t)t * a.B * 3, a.flags ? a.flags + (size_t)tc * a.B : nullptr, a.B, k, a.logn,
+  bin_visibilities<TILES>(a.uvw + (size_t)t * a.B * 3, a.flags ? a.flags + (size_t)tc * a.B : nullptr, a.B, k, a.logn,
                    a.log_strip, a.ku_limit, a.plc + (size_t)tcl * 2 * a.B, a.strip_off + (size_t)tcl * (nstrips + 1),
                    a.n_kept + tcl, a.n_out ? a.n_out + tc : nullptr, a.cell_idx ? a.cell_idx + (size_t)tc * a.B : nullptr,
                    sh, a.ext ? a.ext + tcl : nullptr);
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bin(BinArgs a) {
 
 hipError_t launch_bin(const BinArgs& a, hipStream_t s) {
   if (a.Q <= 0) return hipSuccess;
-  if (a.rows) k_bin<true><<<a.Q, kBinThreads, 0, s>>>(a);
+  if (a.tiles) k_bin<true><<<a.Q, kBinThreads, 0, s>>>(a);
   else k_bin<false><<<a.Q, kBinThreads, 0, s>>>(a);
   return hipGetLastError();
 }
@@ -352,26 +352,35 @@ hipError_t launch_image_average(const float* in, int T, int C, int P, int logn, 
 }
 
 // ---------------------------------------------------------------- full grid (blink_grid)
-// A workgroup writes `PART` consecutive cells of an image: it clears them in LDS, adds the placements
-// of its strip of rows that lie in them, and stores them as whole 16-byte-per-lane lines. Bound by the
-// writes; short parts so that several workgroups share a compute unit and their chains (offsets,
-// records, visibilities, LDS atomics, stores) overlap. The parts and polarisations of a strip are
-// placed 8 workgroups apart: they share one XCD's L2, which then reads the strip's records once.
-// 96 grids of 512^2 with counts of 48 pairs (252 MB): 84 us (112 with parts of 2048 cells, 101 with 8192, 35
-// without the placements); with strips of 16 columns, one
-// workgroup per compute unit, 164 us.
+// A workgroup writes H x W cells of an image (64 x 64): it clears them in LDS, adds the placements of its
+// tile that lie in them, and stores them as whole 512-byte runs. Bound by the writes; parts of 4096 cells so
+// that several workgroups share a compute unit and their chains (offsets, records, visibilities, LDS
+// atomics, stores) overlap. Tiles have both sides short so that a coverage along either axis (an east-west
+// array, v = 0) spreads over many. The same tile of all pairs comes before the next one, the tiles with the
+// dense centre first, so that these spread over the XCDs and no long one comes last; the parts and polarisations
+// of a tile are placed 8 workgroups apart: they share one XCD's L2, which then reads its records once.
+// 96 grids of 512^2 with counts of 48 pairs (252 MB): 67 us (strips of rows, 8192 cells each: 84; strips of 16
+// columns, one workgroup per compute unit, 164); 128 grids of 256^2 with v = 0 throughout: 62 us a call
+// (strips of rows: 377, of columns: 90).
 template <int LOGN, bool UNIFORM, bool COUNT>
 __global__ __launch_bounds__(kGridThreads) void k_grid_full(GridArgs a) {
-  constexpr int N = 1 << LOGN, CELLS = GridCfg<LOGN>::S * N;
-  constexpr int PART = CELLS < kGridPart ? CELLS : kGridPart, PARTS = CELLS / PART, STRIPS = N / GridCfg<LOGN>::S;
+  using Cfg = GridCfg<LOGN>;
+  constexpr int N = 1 << LOGN, H = Cfg::H, W = Cfg::W, PART = H * W, PARTS = Cfg::PARTS;
+  constexpr int TR = N / H, TC = N / Cfg::TW, STRIPS = TR * TC;
+  static_assert(STRIPS == N / Cfg::S && PART % 4 == 0, "a tile has as many cells as a strip");
   constexpr bool COUNTS = UNIFORM || COUNT;
   __shared__ __align__(16) float2 sbuf[PART];
   __shared__ __align__(16) unsigned scnt[COUNTS ? PART : 4];
   __shared__ int s_tmp;
   const unsigned share = PARTS * a.P, sub = blockIdx.x / 8 % share, item = blockIdx.x / (8 * share) * 8 + blockIdx.x % 8;
   if (item >= (unsigned)a.Q * STRIPS) return;      // uniform over the workgroup
-  const int tcl = item / STRIPS, strip = item % STRIPS, p = sub / PARTS, img = tcl * a.P + p;
-  const unsigned cell0 = strip * CELLS + sub % PARTS * PART;
+  const int tile = item / a.Q, tcl = item - tile * a.Q, p = sub / PARTS, img = tcl * a.P + p;
+  const int jr = tile / TC, tr = jr & 1 ? TR - 1 - jr / 2 : jr / 2, tc = tile % TC, strip = tr * TC + tc;
+  const int row0 = tr * H, col0 = tc * Cfg::TW;
+  // of two parts, one takes the left columns of the tile's upper rows and the right ones of its lower rows
+  static_assert(PARTS == 1 || PARTS == 2, "parts of a tile");
+  const int part = (sub + item / 8) % PARTS;       // (in turn, so that busy parts don't meet on every other compute unit)
+  auto left = [&](int row) { return PARTS == 1 ? 0 : W * (part ^ (row / (H / 2))); };
   const int* so = a.strip_off + (size_t)tcl * (STRIPS + 1);
   const int o0 = so[strip], o1 = so[strip + 1];
   const int2* plc = a.plc + (size_t)tcl * 2 * a.B;
@@ -391,8 +400,9 @@ __global__ __launch_bounds__(kGridThreads) void k_grid_full(GridArgs a) {
     for (int j = 0; j < kGridBatch; ++j) r[j] = plc[i + j * kGridThreads < o1 ? i + j * kGridThreads : o0];
 #pragma unroll
     for (int j = 0; j < kGridBatch; ++j) {
-      const bool in = i + j * kGridThreads < o1 && (unsigned)r[j].x - cell0 < (unsigned)PART;
-      r[j].x = in ? r[j].x - (int)cell0 : -1;
+      const int row = (r[j].x >> LOGN) - row0, col = (r[j].x & (N - 1)) - col0 - left(row);
+      const bool in = i + j * kGridThreads < o1 && (unsigned)col < (unsigned)W;
+      r[j].x = in ? row * W + col : -1;
       v[j] = V[in ? r[j].y & 0x7fffffff : 0];
     }
 #pragma unroll
@@ -418,21 +428,24 @@ __global__ __launch_bounds__(kGridThreads) void k_grid_full(GridArgs a) {
     block_add_to_global(occ, &s_tmp, a.occ + img);
     __syncthreads();
   }
+  // where cell i of the part (its row i / W, column i % W) lies from the tile's first
+  auto at = [&](int i) { return (size_t)(i / W) * N + left(i / W) + i % W; };
+  const size_t cell0 = (size_t)row0 * N + col0;
   float2* G = a.grids + (size_t)img * N * N + cell0;
   if (((uintptr_t)a.grids & 15) == 0) {
-    for (int i = threadIdx.x; i < PART / 2; i += kGridThreads)
-      reinterpret_cast<float4*>(G)[i] = reinterpret_cast<const float4*>(sbuf)[i];
+    for (int i = 2 * threadIdx.x; i < PART; i += 2 * kGridThreads)
+      *reinterpret_cast<float4*>(G + at(i)) = *reinterpret_cast<const float4*>(sbuf + i);
   } else {                                         // the caller's array may start at any complex value
-    for (int i = threadIdx.x; i < PART; i += kGridThreads) G[i] = sbuf[i];
+    for (int i = threadIdx.x; i < PART; i += kGridThreads) G[at(i)] = sbuf[i];
   }
   if constexpr (COUNT) {
     if (p == 0) {
       int32_t* cnt = a.counts + (size_t)tcl * N * N + cell0;
       if (((uintptr_t)a.counts & 15) == 0) {
-        for (int i = threadIdx.x; i < PART / 4; i += kGridThreads)
-          reinterpret_cast<int4*>(cnt)[i] = reinterpret_cast<const int4*>(scnt)[i];
+        for (int i = 4 * threadIdx.x; i < PART; i += 4 * kGridThreads)
+          *reinterpret_cast<int4*>(cnt + at(i)) = *reinterpret_cast<const int4*>(scnt + i);
       } else {
-        for (int i = threadIdx.x; i < PART; i += kGridThreads) cnt[i] = (int32_t)scnt[i];
+        for (int i = threadIdx.x; i < PART; i += kGridThreads) cnt[at(i)] = (int32_t)scnt[i];
       }
     }
   }
@@ -503,9 +516,8 @@ int grid_strip_width(int logn) {
 template <int LOGN>
 struct GridFullL {
   static hipError_t run(const GridArgs* a, hipStream_t s) {
-    constexpr int N = 1 << LOGN;
-    constexpr int CELLS = GridCfg<LOGN>::S * N, PARTS = CELLS < kGridPart ? 1 : CELLS / kGridPart;
-    const long items = (long)a->Q * (N / GridCfg<LOGN>::S), blocks = (items + 7) / 8 * 8 * PARTS * a->P;
+    using Cfg = GridCfg<LOGN>;
+    const long items = (long)a->Q * (Cfg::N / Cfg::S), blocks = (items + 7) / 8 * 8 * Cfg::PARTS * a->P;
     if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
     const unsigned grid = (unsigned)blocks;
     if (a->uniform && a->counts) k_grid_full<LOGN, true, true><<<grid, kGridThreads, 0, s>>>(*a);

@@ -28,13 +28,15 @@ struct ColSmax {
 // row-pair transforms per workgroup. Smaller grids get one variant each.
 constexpr int kTunedLogn = 8;
 
+constexpr int kGridPart = 4096;              // cells of a workgroup of the full grid
 template <int LOGN>
 struct GridCfg {
   static constexpr int N = 1 << LOGN;
-  static constexpr int S = pow2_floor(cmin(N, (128 * 1024) / (N * 12)));   // rows of a strip
+  static constexpr int S = pow2_floor(cmin(N, (128 * 1024) / (N * 12)));   // a tile has S N cells
+  static constexpr int H = cmin(N, 1 << kLogTileRows), TW = S * N / H;     // of H rows and TW columns
+  static constexpr int W = cmin(N, kGridPart / H), PARTS = TW / W;         // a workgroup's columns of it
 };
 constexpr int kGridThreads = 512;
-constexpr int kGridPart = 4096;              // cells of a workgroup
 constexpr int kGridBatch = 4;                // records a thread loads together
 
 // A row variant fits when TPB transforms of N padded points plus the twiddle table fit in LDS.

@@ -30,7 +30,7 @@ struct BinArgs {
   const double* freq;       // [C]
   const uint8_t* flags;     // [T][C][B] or null
   int tc0, Q, C, B, logn, log_strip, ku_limit, P;
-  int rows;                 // strips of rows instead of columns
+  int tiles;                // tiles of as many cells instead of strips of columns
   double pixel_scale;
   int2* plc;                // [Q][2B]
   int* strip_off;           // [Q][nstrips+1]
