@@ -610,13 +610,13 @@ blink_status blink_ifft2d(blink_ctx ctx, const blink_cf32* grids, const double* 
 }
 
 struct FoldLayout {
-  size_t hdr, rows, rec, val, vc, total;
+  size_t hdr, rows, rec, val, vc, place, coef, total;
   int ent_stride;
   bool ok;
 };
 
-// Arrays of the folded path for Q pairs of P images each.
-static FoldLayout fold_layout(size_t Q, int P, int B, bool corrected) {
+// Arrays of the folded path for Q pairs of P images each; values: a launch of its own writes the values.
+static FoldLayout fold_layout(size_t Q, int P, int B, bool corrected, bool values) {
   Carve c;
   FoldLayout L;
   L.ent_stride = blink::fold_entries(B);
@@ -625,6 +625,8 @@ static FoldLayout fold_layout(size_t Q, int P, int B, bool corrected) {
   L.rec = c.take(Q, (size_t)L.ent_stride * sizeof(uint32_t));
   L.val = c.take(Q * (size_t)P, (size_t)L.ent_stride * sizeof(float2));
   L.vc = corrected ? c.take(Q * (size_t)P, (size_t)B * sizeof(float2)) : 0;
+  L.place = values ? c.take(Q, (size_t)B * sizeof(uint32_t)) : 0;
+  L.coef = values ? c.take(Q, (size_t)B * sizeof(float2)) : 0;
   L.total = c.off;
   L.ok = c.ok;
   return L;
@@ -676,26 +678,33 @@ static blink_status image_batch(blink_ctx ctx, const blink_cf32* vis, const uint
   // baselines for few images where the two-pass form is at its best: uniform weighting (8128 baselines: 1 image
   // 46 against 33 us, 96 images 53 against 52, 128 images 56 against 68) and the split FP16 form (natural: 1 image
   // 37 against 34, 64 images 39 against 43); natural FP32 and BF16 gain from one image on (36 against 39, 37
-  // against 44). Up to 128^2 it always loses (600 images, 8128 baselines: 120 against 108 us; 300, 10296
+  // against 44), but for four images of one pair, whose values are another launch (44 against 41; 64: 47 against
+  // 48), and in workspaces whose lists outgrow the chunks (64 images of 4 pairs of 16384: 131
+  // against 69). Up to 128^2 it always loses (600 images, 8128 baselines: 120 against 108 us; 300, 10296
   // baselines: 105 against 84). The two-pass form serves those and larger arrays.
   // A workspace has to hold one pair of the two-pass form, whichever form the call takes: callers meet one limit.
   const ImageLayout one = image_layout(1, P, B, logn, weighting, 1, corrected);
   if (!one.ok || one.total > workspace_bytes)
     return fail(ctx, BLINK_ERR_SIZE, "workspace of %zu bytes is smaller than one (t,c) pair needs (%zu)", workspace_bytes,
                 one.total);
-  const size_t n_img256 = B < 4096 ? 192 : weighting ? 128 : precision == BLINK_PREC_SPLIT_F16 ? 64 : 1;
+  const size_t n_img256 = B < 4096 ? 192 : weighting ? 128 : precision == BLINK_PREC_SPLIT_F16 || P >= 4 ? 64 : 1;
   const bool folds = !two_pass && (logn > 8 || (logn == 8 && n_tc * P >= n_img256));
   if (folds && B > 0 && B <= blink::kFoldMaxB) {
     const int m = blink::fold_rows(logn);
+    // The binning's workgroup of a pair writes the values of its images in turn. Where there are more than a few of
+    // them and too few pairs to fill the chip, a launch with a workgroup per image writes them (one pair of
+    // 8128 baselines, 512^2: 16 images 84 -> 47 us a call, 64 images 259 -> 64).
+    const bool values = P >= 4 && n_tc < 256 && n_tc * P < (size_t)1 << 22;
     const size_t Q = largest_fitting_chunk(n_tc, workspace_bytes,
-                                           [&](size_t q) { return fold_layout(q, P, B, corrected).total; });
-    if (Q > 0 && Q * P <= (size_t)INT32_MAX) {
+                                           [&](size_t q) { return fold_layout(q, P, B, corrected, values).total; });
+    const bool enough = logn > 8 || Q == n_tc || Q * P >= 192;
+    if (Q > 0 && enough && Q * P <= (size_t)INT32_MAX) {
       DeviceGuard g(ctx->device);
       if (g.err != hipSuccess) return hip_fail(ctx, g.err, "hipSetDevice");
       hipStream_t s = (hipStream_t)hip_stream;
       char* ws = (char*)workspace;
       const size_t N = size_t(1) << logn;
-      const FoldLayout L = fold_layout(Q, P, B, corrected);
+      const FoldLayout L = fold_layout(Q, P, B, corrected, values);
       int logm = 0;
       while ((1 << logm) < m) ++logm;
       for (size_t tc0 = 0; tc0 < n_tc; tc0 += Q) {
@@ -721,6 +730,8 @@ static blink_status image_batch(blink_ctx ctx, const blink_cf32* vis, const uint
         ba.rec = (uint32_t*)(ws + L.rec);
         ba.val = (float2*)(ws + L.val);
         ba.n_out = n_out;
+        ba.place = values ? (uint32_t*)(ws + L.place) : nullptr;
+        ba.coef = values ? (float2*)(ws + L.coef) : nullptr;
         hipError_t e;
         if (corrected) {
           float2* vc = (float2*)(ws + L.vc);

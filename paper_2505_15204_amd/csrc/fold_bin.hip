@@ -171,7 +171,8 @@ __device__ __forceinline__ void fold_bin(const double* __restrict__ uvw, const u
                                          int logn, int logm, int shift, const float2* __restrict__ vis, int P,
                                          size_t vis_stride, FoldHeader* hdr, uint32_t* __restrict__ rows,
                                          uint32_t* __restrict__ rec, float2* __restrict__ val, size_t val_stride,
-                                         int* nout_out, FoldShared<STAGE>& sh) {
+                                         int* nout_out, FoldShared<STAGE>& sh, uint32_t* __restrict__ place = nullptr,
+                                         float2* __restrict__ coef = nullptr) {
   const int N = 1 << logn, mask = N - 1, HALF = N / 2, M = 1 << logm, cells = M * HALF;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const double half = (double)HALF;
@@ -396,6 +397,24 @@ __device__ __forceinline__ void fold_bin(const double* __restrict__ uvw, const u
   __syncthreads();
   if (UNIFORM && tid == 0) hdr->occ = sh.occ;
   const float scale = inverse_weight(UNIFORM ? (double)sh.occ : 2.0 * (double)sh.kept);
+  // factors of a visibility's parts: its weight over the image's, with (-1)^(ku + kv) when the image is
+  // shifted, and conjugated where the placement is the mirror's
+  auto factors = [&](int cd, float w) {
+    const int cell = cd & 0x1fff;
+    const bool neg = shift && ((((cd >> 13) & 0x7ff) << logm) + (cell >> (logn - 1)) + cell) & 1;
+    const float ws = w * scale, re = neg ? -ws : ws;
+    return make_float2(re, (cd >> 24) & 1 ? -re : re);
+  };
+  if (place) {                                   // uniform over the workgroup: k_fold_values writes the values
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int b = i * kFoldThreads + tid;
+      if (b >= B) continue;
+      place[b] = code[i] < 0 ? ~0u : at[i];
+      coef[b] = code[i] < 0 ? make_float2(0.f, 0.f) : factors(code[i], wt[i]);
+    }
+    return;
+  }
   for (int p = 0; p < P; ++p) {
     for (int w0 = 0; w0 < n_ent; w0 += VW) {
       // Addresses and signs are formed again for every polarisation and window: kept over these loops
@@ -414,14 +433,11 @@ __device__ __forceinline__ void fold_bin(const double* __restrict__ uvw, const u
         for (int i = 0; i < kFoldLoad; ++i) {
           int cd = code[c + i];                  // (see t)
           asm volatile("" : "+v"(cd));
-          const int cell = cd & 0x1fff;
           if (cd < 0) continue;
-          // (-1)^(ku + kv) when the image is shifted
-          const bool neg = shift && ((((cd >> 13) & 0x7ff) << logm) + (cell >> (logn - 1)) + cell) & 1;
-          const float ws = wt[c + i] * scale, re = neg ? -ws : ws, im = (cd >> 24) & 1 ? -re : re;
+          const float2 f = factors(cd, wt[c + i]);
           const unsigned a0 = (at[c + i] & 0xffffu) - (unsigned)w0, a1 = (at[c + i] >> 16) - (unsigned)w0;
-          if (a0 < (unsigned)VW) sh.val[a0] = make_float2(v[i].x * re, v[i].y * im);
-          if (at[c + i] < 0xffff0000u && a1 < (unsigned)VW) sh.val[a1] = make_float2(v[i].x * re, -(v[i].y * im));
+          if (a0 < (unsigned)VW) sh.val[a0] = make_float2(v[i].x * f.x, v[i].y * f.y);
+          if (at[c + i] < 0xffff0000u && a1 < (unsigned)VW) sh.val[a1] = make_float2(v[i].x * f.x, -(v[i].y * f.y));
         }
       }
       if (pad_at < n_ent && (unsigned)(pad_at - w0) < (unsigned)VW) sh.val[pad_at - w0] = make_float2(0.f, 0.f);
@@ -432,7 +448,7 @@ __device__ __forceinline__ void fold_bin(const double* __restrict__ uvw, const u
   }
 }
 
-template <int NB, bool UNIFORM, int STAGE>
+template <int NB, bool UNIFORM, int STAGE, bool VALUES>
 __global__ __launch_bounds__(kFoldThreads, NB > 8 ? 4 : 8) void k_fold_bin(FoldBinArgs a) {
   __shared__ FoldShared<STAGE> sh;
   const int q = blockIdx.x;
@@ -443,7 +459,46 @@ __global__ __launch_bounds__(kFoldThreads, NB > 8 ? 4 : 8) void k_fold_bin(FoldB
                                a.logm, a.shift, a.vis + (size_t)q * a.P * a.B, a.P, (size_t)a.B, a.hdr + q,
                                a.rows + (size_t)q * kFoldRows, a.rec + (size_t)q * a.ent_stride,
                                a.val + (size_t)q * a.P * a.ent_stride, (size_t)a.ent_stride,
-                               a.n_out ? a.n_out + tc : nullptr, sh);
+                               a.n_out ? a.n_out + tc : nullptr, sh, VALUES ? nullptr : a.place + (size_t)q * a.B,
+                               VALUES ? nullptr : a.coef + (size_t)q * a.B);
+}
+
+// The values of one image (workgroup), where the binning's workgroups, one a pair, would write too many of
+// them one after the other: one pair of 8128 baselines takes 3 us for each polarisation. (16 polarisations of one pair,
+// 512^2: 84 us a call with the values in the binning, 47 so, 51 in the two-pass form.)
+__global__ __launch_bounds__(kFoldThreads) void k_fold_values(FoldBinArgs a) {
+  constexpr int VW = 8192;                         // positions put in order at a time
+  __shared__ float2 out[VW];
+  const int tid = threadIdx.x, q = blockIdx.x / a.P;
+  const int n_ent = a.hdr[q].first_over + a.hdr[q].n_over;
+  const uint32_t* place = a.place + (size_t)q * a.B;
+  const float2* coef = a.coef + (size_t)q * a.B;
+  const float2* vis = a.vis + (size_t)blockIdx.x * a.B;
+  float2* val = a.val + (size_t)blockIdx.x * a.ent_stride;
+  for (int w0 = 0; w0 < n_ent; w0 += VW) {
+    for (int j = tid; j < VW; j += kFoldThreads) out[j] = make_float2(0.f, 0.f);   // also the diagonals' padding
+    __syncthreads();
+    for (int b0 = tid; b0 < a.B; b0 += kFoldLoad * kFoldThreads) {
+      uint32_t at[kFoldLoad];
+      float2 f[kFoldLoad], v[kFoldLoad];
+#pragma unroll
+      for (int i = 0; i < kFoldLoad; ++i) {
+        const int b = b0 + i * kFoldThreads < a.B ? b0 + i * kFoldThreads : b0;
+        at[i] = place[b];
+        f[i] = coef[b];
+        v[i] = vis[b];
+      }
+#pragma unroll
+      for (int i = 0; i < kFoldLoad; ++i) {
+        const unsigned a0 = (at[i] & 0xffffu) - (unsigned)w0, a1 = (at[i] >> 16) - (unsigned)w0;
+        if ((at[i] & 0xffffu) != 0xffffu && a0 < (unsigned)VW) out[a0] = make_float2(v[i].x * f[i].x, v[i].y * f[i].y);
+        if (at[i] < 0xffff0000u && a1 < (unsigned)VW) out[a1] = make_float2(v[i].x * f[i].x, -(v[i].y * f[i].y));
+      }
+    }
+    __syncthreads();
+    for (int j = tid; j < VW && w0 + j < n_ent; j += kFoldThreads) val[w0 + j] = out[j];
+    __syncthreads();
+  }
 }
 
 // Uneven batches: workgroup w bins the image at position pos0 + w of the descriptor pass's order.
@@ -489,17 +544,30 @@ hipError_t launch_fold_desc(const DescArgs& a, int prec, unsigned items, hipStre
   }
 }
 
+template <bool VALUES>
+static void bin_pairs(const FoldBinArgs& a, hipStream_t s) {
+  // uniform weighting keeps every record in the LDS at once (two per baseline at most)
+  if (a.B <= 8 * kFoldThreads) {
+    if (a.uniform) k_fold_bin<8, true, 68 * 1024, VALUES><<<a.Q, kFoldThreads, 0, s>>>(a);
+    else k_fold_bin<8, false, 68 * 1024, VALUES><<<a.Q, kFoldThreads, 0, s>>>(a);
+  } else {
+    if (a.uniform) k_fold_bin<16, true, 132 * 1024, VALUES><<<a.Q, kFoldThreads, 0, s>>>(a);
+    else k_fold_bin<16, false, 132 * 1024, VALUES><<<a.Q, kFoldThreads, 0, s>>>(a);
+  }
+}
+
 hipError_t launch_fold_bin(const FoldBinArgs& a, hipStream_t s) {
   if (a.Q <= 0) return hipSuccess;
   if (a.B <= 0 || a.B > kFoldMaxB) return hipErrorInvalidValue;
-  // uniform weighting keeps every record in the LDS at once (two per baseline at most)
-  if (a.B <= 8 * kFoldThreads) {
-    if (a.uniform) k_fold_bin<8, true, 68 * 1024><<<a.Q, kFoldThreads, 0, s>>>(a);
-    else k_fold_bin<8, false, 68 * 1024><<<a.Q, kFoldThreads, 0, s>>>(a);
-  } else {
-    if (a.uniform) k_fold_bin<16, true, 132 * 1024><<<a.Q, kFoldThreads, 0, s>>>(a);
-    else k_fold_bin<16, false, 132 * 1024><<<a.Q, kFoldThreads, 0, s>>>(a);
+  if (!a.place) {
+    bin_pairs<true>(a, s);
+    return hipGetLastError();
   }
+  if ((long)a.Q * a.P >= 1L << 22) return hipErrorInvalidValue;   // threads of a launch stay below 2^32
+  bin_pairs<false>(a, s);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  k_fold_values<<<(unsigned)(a.Q * a.P), kFoldThreads, 0, s>>>(a);
   return hipGetLastError();
 }
 

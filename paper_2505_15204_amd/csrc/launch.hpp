@@ -136,6 +136,8 @@ struct FoldBinArgs {
   uint32_t* rec;            // [Q][ent_stride]: placement records {8 (kv / M), LDS index << 17}
   float2* val;              // [Q][P][ent_stride]: the placements' values over the image's weight
   int32_t* n_out;           // [T][C] or null (global)
+  uint32_t* place;          // [Q][B] positions of a baseline's placement and its mirror (16 bits each, 0xffff: none), or null
+  float2* coef;             // [Q][B] factors of its visibility's parts; with place, a launch of its own writes the values
 };
 hipError_t launch_fold_bin(const FoldBinArgs& a, hipStream_t s);
 

@@ -35,12 +35,12 @@ def row_launches(torch, ctx, call):
     return launches
 
 
-def image_call(torch, ctx, B, N, C, weighting, prec):
+def image_call(torch, ctx, B, N, C, weighting, prec, P=1):
     g = np.random.default_rng(B + N)
     d = "cuda:0"
     uvw = np.zeros((1, B, 3))
     uvw[0, :, :2] = g.uniform(-N / 2 + 1, N / 2 - 1, (B, 2)) / (FREQ / 299792458.0 * (N * DL))
-    vis = torch.randn((1, C, 1, B), device=d, dtype=torch.complex64)
+    vis = torch.randn((1, C, P, B), device=d, dtype=torch.complex64)
     uvw, freq = torch.from_numpy(uvw).to(d), torch.full((C,), FREQ, dtype=torch.float64, device=d)
     return lambda: ctx.blink_image_batch(vis, None, uvw, freq, N, DL, weighting, precision=prec)
 
@@ -54,6 +54,13 @@ def image_call(torch, ctx, B, N, C, weighting, prec):
 def test_image_batch(torch, ctx, B, N, C, weighting, prec, folded):
     print(f"[gpu-case] route B={B} N={N} C={C} w={weighting} prec={prec}", flush=True)
     assert (row_launches(torch, ctx, image_call(torch, ctx, B, N, C, weighting, prec)) == 0) == folded
+
+
+# several images of a pair, and lists that outgrow the workspace query at 256^2
+@pytest.mark.parametrize("B,C,P,folded", [(8128, 1, 3, True), (8128, 1, 4, False), (8128, 4, 16, True), (16384, 4, 16, False)])
+def test_polarisations(torch, ctx, B, C, P, folded):
+    print(f"[gpu-case] route B={B} C={C} P={P}", flush=True)
+    assert (row_launches(torch, ctx, image_call(torch, ctx, B, 256, C, 0, 0, P)) == 0) == folded
 
 
 def desc_call(torch, ctx, N, B, n_img):

@@ -100,7 +100,7 @@ def test_chunks(torch, ctx, prec, weighting, corrected):
 def test_lists_that_do_not_fit(torch, ctx, corrected):
     import paper_2505_15204_amd as blink
     N, P = 256, 2
-    prob = problem(181, N, 1, 3, P)
+    prob = problem(181, N, 1, 1, P)
     B = prob[2].shape[-1]
     ref = oracle.image_batch(prob[2], prob[3], prob[0], prob[1], N, DL, 0)
     fits = lists(B, P, corrected)
