@@ -36,8 +36,8 @@ def log(msg):
 
 
 # device sources of the batched FP32 imaging kernels (the host code in api.hip, the correlator, the
-# uneven-batch kernel and the split forms' instantiation unit do not change their code; the launch
-# configuration is checked separately through the plan)
+# uneven-batch kernel and the split forms' instantiation unit do not change their code; the folded
+# form has no plan)
 IMAGING_KERNEL_SOURCES = ("fft_device.hpp", "fold.hip", "fold_bin.hip", "fold_device.hpp", "imaging_device.hpp",
                           "launch.hpp", "split_fft.hpp")
 
@@ -55,16 +55,16 @@ def kernel_source_hash():
     return h.hexdigest()[:16]
 
 
-def counter_traffic(tag, kernel, plan):
+def counter_traffic(tag, kernel):
     """Scaled FETCH_SIZE + WRITE_SIZE bytes per launch of `kernel` from profiles/<tag>_hbm_counters.md,
-    or None when absent or taken from different kernel sources or a different execution plan."""
+    or None when absent or taken from different kernel sources."""
     path = os.path.join(ROOT, "profiles", f"{tag}_hbm_counters.md")
     if not os.path.exists(path):
         return None
     for ln in open(path):
         if ln.startswith("traffic-json:"):
             rec = json.loads(ln.split(":", 1)[1])
-            if rec.get("source_hash") != kernel_source_hash() or rec.get("plan") != plan:
+            if rec.get("source_hash") != kernel_source_hash():
                 return None
             return rec.get("bytes_per_launch", {}).get(kernel)
     return None
@@ -413,7 +413,7 @@ def bench_phase2(ctx, torch, blink, synth, steps, warmup):
                        "20 x 1 ms time steps, 2048^2 FP32 grid, 0.75 arcmin pixels, uniform weighting, 10% flags; "
                        "one step = one time step = 6144 images in 4 calls of 768 channels",
            "images_per_step": C * P, "steps": steps, "images_per_s": round(value, 1),
-           "ms_per_step": round(ms / steps, 3), "plan": ctx.get_plan(N, 1),
+           "ms_per_step": round(ms / steps, 3),
            "path_roofline": {"bytes_per_image_model": per_image,
                              "column_extent": {"mean_columns": round(ext, 1), "of": N // 2},
                              "achieved_GB_s": round(value * per_image / 1e9, 1),
@@ -489,7 +489,8 @@ def main():
     ap.add_argument("--cpu-seconds", type=float, default=15.0, help="budget of the CPU oracle sample")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--autotune", action="store_true",
-                    help="tune the execution plan on time step 0 instead of loading the committed plan file")
+                    help="tune the two-pass form's execution plan on time step 0 instead of loading the committed plan file "
+                         "(the convolutional path takes it; the headline's folded form has none)")
     ap.add_argument("--save-plans", default="", help="write the context's plans (JSON) to this path")
     ap.add_argument("--plan", default="", help="force a plan col_strip,row_block,group[,col_loop]")
     ap.add_argument("--no-forms", action="store_true",
@@ -498,9 +499,6 @@ def main():
     ap.add_argument("--desc-form", choices=("auto", "staged", "persistent"), default="auto",
                     help="form of the uneven batch: auto runs the descriptor autotuner per precision (default); "
                          "staged or persistent fix the form with its default plan (for profiles)")
-    ap.add_argument("--no-cache-probe", action="store_true",
-                    help="accepted for older command lines: the pass with image groups beyond the last-level cache "
-                         "went with the half spectra in memory")
     ap.add_argument("--forms", default="all",
                     help="comma-separated subset of the forms measured beside the headline: split, conv, "
                          "corrected, average, correlator, dedispersion, precision, uneven, phase2 (default all)")
@@ -563,13 +561,13 @@ def main():
         ctx.load_plans(blink.PLANS_PATH)
         tune = {"source": os.path.relpath(blink.PLANS_PATH, ROOT)}
     else:
-        log("autotuning the execution plan on time step 0")
+        log("autotuning the two-pass form's execution plan on time step 0")
         t0 = time.perf_counter()
         plan, best_ms = ctx.autotune_image_batch(d["vis"][0:1], d["flags"][0:1], d["uvw_m"][0:1], d["freq_hz"], N,
                                                  spec.pixel_scale, 0, out=images, workspace=ws)
         tune = {"source": "autotuned", "best_step_ms": round(best_ms, 4),
                 "seconds": round(time.perf_counter() - t0, 2)}
-        log(f"plan {plan}: {best_ms:.3f} ms per step")
+        log(f"two-pass plan {plan}: {best_ms:.3f} ms per step")
     if args.save_plans:
         ctx.save_plans(args.save_plans)
     plan = ctx.get_plan(N, 0)
@@ -592,7 +590,7 @@ def main():
     dom = max((k for k in kernels if k in ub), key=lambda k: kernels[k]["total_ms"])
     roof = {"kernel": dom, "bound": "hbm", "achieved": kernels[dom]["achieved_GB_s"], "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": kernels[dom]["frac_hbm"],
-            "traffic": counter_traffic("vcs1024_fp32", dom, plan)}
+            "traffic": counter_traffic("vcs1024_fp32", dom)}
     per_image = path_bytes_per_image(spec)
     path = {"bytes_per_image_model": per_image,
             "column_extent": {"mean_columns": round(ext, 1), "of": N // 2},
@@ -624,8 +622,7 @@ def main():
                                   kernel_unit_bytes(spec))
                 v = fs * C * P / (ms / 1e3)
                 forms["vcs-1024"][name] = {"images_per_s": round(v, 1), "vs_fp32": round(v / value, 4),
-                                           "plan": ctx.get_plan(N, 0, prec),
-                                           "kernels": {k: fk[k] for k in ("grid_colfft", "row_fft") if k in fk}}
+                                           "kernels": {k: fk[k] for k in ("bin", "grid_colfft") if k in fk}}
                 log(f"{name}: {v:.0f} images/s ({v / value:.3f} x FP32)")
         if "conv" in want:
             # Convolutional gridding (W = 8, beta = 18.4) on the same workload, FP32.
@@ -730,8 +727,7 @@ def main():
             "grid_n": N,
             "baselines": B,
             "path": "fp32: bin -> folded grid + column FFT + row FFT (C2R) per class of rows",
-            "plan": plan,
-            "autotune": tune,
+            "two_pass_plan": {"used_by": "conv (row block and group); none of the folded forms", "plan": plan, **(tune or {})},
         },
         "roofline": roof,
         "path_roofline": path,
