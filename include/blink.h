@@ -322,11 +322,12 @@ blink_status blink_dedisperse(blink_ctx ctx, const float *images, int T, int C, 
  *                          through a per-workgroup intermediate slot;
  *   BLINK_DESC_STAGED      one launch bins every image and one images them all, the folded form of
  *                          blink_image_batch for every size (for as many images at a time as the
- *                          workspace holds). With more than 16384 baselines in an image, or a
- *                          workspace that holds fewer than 64 images: per chunk of images of one grid
- *                          size whose half spectra fit a 256 MiB buffer (sized for the last-level
- *                          cache), a column launch and a row launch of the two-pass kernels for
- *                          that size.
+ *                          workspace holds). With more than 16384 baselines in an image, a
+ *                          workspace that holds fewer than 64 images, or nothing but small grids (64^2
+ *                          and below, unless the images hold thousands of baselines): per chunk of images
+ *                          of one grid size whose half spectra fit a 256 MiB buffer (sized for the
+ *                          last-level cache), a column launch and a row launch of the two-pass
+ *                          kernels for that size.
  * In both, workgroups never wait for each other (the staged launches are ordered by the stream). */
 #define BLINK_DESC_PERSISTENT 0
 #define BLINK_DESC_STAGED 1
@@ -410,10 +411,10 @@ blink_status blink_graph_destroy(blink_graph graph);
  * Not part of the method: how blink_image_batch schedules its kernels for one grid size,
  * weighting and precision form (each has its own plan; blink_ifft2d uses the row_block of the
  * natural-weighting plan of its precision). A plan never changes results beyond rounding order.
- * Plans steer the two-pass form: blink_image_batch and its variants use it for grids below 256 (and
- * small calls at 256), above 16384 baselines and in workspaces too small for the folded form, which
- * has no options;
- * blink_ifft2d and blink_image_batch_conv always do.
+ * Plans steer the two-pass form: blink_image_batch and its variants use it for grids below 256 (at
+ * 256 for calls of few images, by weighting and precision), above 16384 baselines and in workspaces
+ * too small for the folded form's lists; the folded form has no options. blink_ifft2d and
+ * blink_image_batch_conv always take them.
  * Fields:
  *   col_strip  columns of the half spectrum per workgroup of the fused gridding + column FFT kernel
  *   row_block  row-pair transforms per workgroup of the row FFT kernel

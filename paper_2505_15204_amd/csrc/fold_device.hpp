@@ -12,12 +12,12 @@
 // class reads the image's placements once more (from L2: 8 B per placement), which costs far less
 // than the half spectrum's trip to memory and back (16 B per column and row of the grid).
 //
-// What bounds it: 16 images of 1024^2 write 67 MB, 10 us at the rate of a fill (6.8 TB/s); the kernel
-// takes 23 us of it per 16 images with two workgroups per compute unit, whose phases overlap: VALU
-// issue 60% of the time, the fold's loads and barriers the rest (without the fold it takes 15 us).
-// One workgroup of M N = 32768 per compute unit halves the fold's work but runs its phases one
-// after the other (28 us); M N = 16384 measured faster at 256^2 .. 1024^2 and equal above. The
-// two-pass form (column pass, half spectrum, row pass) took 27 us in its launches plus its tails.
+// What bounds it: 1536 images of 1024^2 write 6.44 GB, 0.94 ms at the rate of a fill (6.87 TB/s); the kernel
+// takes 2.18 ms with two workgroups per compute unit, whose phases overlap: VALU issue 64% of the time, waves
+// waiting 35% of theirs (16% for the LDS). A call on 256 images takes 400 us with 8128 baselines, of which 87 are the
+// fold: 313 with 45. One workgroup of M N = 32768 per compute unit halves the fold's work but runs its phases one
+// after the other (2.82 ms against 2.23 when both were built); M N = 16384 measured faster at 256^2 .. 1024^2 and
+// equal above. The two-pass form (column pass, half spectrum, row pass) took 3.9 ms.
 //
 // Placement layout of one (time, channel) pair (k_fold_bin): the placements of one folded cell
 // (k, ku) form a segment; segments are numbered by length, longest first, and stored as jagged
