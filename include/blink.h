@@ -459,7 +459,7 @@ blink_status blink_autotune_image_batch(blink_ctx ctx, const blink_cf32 *vis, co
  * of the entry points above is bracketed by a pair of hipEvents recorded on the caller's stream.
  * Kernel ids: */
 enum {
-    BLINK_KERNEL_BIN = 0,          /* cell indices + strip binning, one workgroup per (t, c) */
+    BLINK_KERNEL_BIN = 0,          /* cell indices + binning, one workgroup per (t, c); folded form: with its values */
     BLINK_KERNEL_GRID = 1,         /* full-grid gridding (blink_grid) */
     BLINK_KERNEL_GRID_COLFFT = 2,  /* blink_image_batch: folded imaging kernel, or gridding + column FFT */
     BLINK_KERNEL_DENSE_COLFFT = 3, /* column FFT of dense grids (blink_ifft2d) */

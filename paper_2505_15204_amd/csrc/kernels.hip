@@ -2,8 +2,8 @@
 //
 //   k_twiddles       FP64 sincospi -> FP32 stage-ordered twiddle table
 //   k_bin            cell indices (FP64 product + rint), flags, out-of-grid drop, counting sort
-//                    of the placements into column strips (Section 6.2.4 gridding, one
-//                    workgroup per (time, channel), shared by the polarisations)
+//                    of the placements into column strips, or tiles of the full grid (Section
+//                    6.2.4 gridding, one workgroup per (time, channel), shared by the polarisations)
 //   k_grid_full      LDS-private tiles -> complex grid in HBM, counts
 //   k_grid_colfft    LDS-private strip grid -> inverse FFT along v -> half-spectrum H
 //   k_dense_colfft   Hermitian part of a dense grid -> inverse FFT along v -> H
@@ -355,8 +355,8 @@ hipError_t launch_image_average(const float* in, int T, int C, int P, int logn, 
 // A workgroup writes H x W cells of an image (64 x 64): it clears them in LDS, adds the placements of its
 // tile that lie in them, and stores them as whole 512-byte runs. Bound by the writes; parts of 4096 cells so
 // that several workgroups share a compute unit and their chains (offsets, records, visibilities, LDS
-// atomics, stores) overlap. Tiles have both sides short so that a coverage along either axis (an east-west
-// array, v = 0) spreads over many. The same tile of all pairs comes before the next one, the tiles with the
+// atomics, stores) overlap. Tiles have both sides short, and their two parts divide them crosswise, so that a
+// coverage along either axis (an east-west array, v = 0) spreads over many. The same tile of all pairs comes before the next one, the tiles with the
 // dense centre first, so that these spread over the XCDs and no long one comes last; the parts and polarisations
 // of a tile are placed 8 workgroups apart: they share one XCD's L2, which then reads its records once.
 // 96 grids of 512^2 with counts of 48 pairs (252 MB): 67 us (strips of rows, 8192 cells each: 84; strips of 16
